@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kBlock) void paged_hash_chunk_kernel(
       }
     };
     B3Cv st;
-    b3_chunk(st, nb, (uint64_t)c, m == 1, load);
+    b3_chunk<kChunkLevels>(st, nb, (uint64_t)c, m == 1, load);
     store_cv(nodes + (base0[i] + t * m + c) * 32, st);
   }
 }
@@ -221,6 +221,9 @@ constexpr int kSubLanes = 64;
 // consecutive banks). The first level is folded straight from the children in
 // memory, so the slots hold at most half of them. m0: the tensor's chunk count,
 // which places ROOT on the compression that leaves the tensor one node.
+// PAIRED: the subtree launches, whose waves share their SIMDs (747 -> 586 us for
+// the first one of the Qwen3-4B large set); the tail has a wave per SIMD at most.
+template <bool PAIRED>
 __device__ __forceinline__ void fold_children(const uint8_t* c, int cur, int64_t m0, int v0, int K,
                                               uint32_t (*lds)[kSubLanes], int lane,
                                               uint32_t (&w)[8]) {
@@ -255,7 +258,8 @@ __device__ __forceinline__ void fold_children(const uint8_t* c, int cur, int64_t
       if (pair) {
         B3Cv cv;
         b3_init(cv);
-        b3_compress(cv, m, 0, 64, flags);
+        if constexpr (PAIRED) b3_compress_paired<1>(cv, m, 0, 64, flags);
+        else b3_compress(cv, m, 0, 64, flags);
 #pragma unroll
         for (int k = 0; k < 8; ++k) m[k] = cv.h[k];
       }
@@ -298,7 +302,7 @@ __global__ __launch_bounds__(kSubLanes) void hash_subtree_kernel(
   const int64_t first = j << K;
   const int cur = (int)(m_lo - first < ((int64_t)1 << K) ? m_lo - first : ((int64_t)1 << K));
   uint32_t w[8];
-  fold_children(in + (base_lo[i] + t * m_lo + first) * 32, cur, m0, v0, K, lds, lane, w);
+  fold_children<true>(in + (base_lo[i] + t * m_lo + first) * 32, cur, m0, v0, K, lds, lane, w);
   uint4* o = reinterpret_cast<uint4*>(out + g * 32);
   o[0] = make_uint4(w[0], w[1], w[2], w[3]);
   o[1] = make_uint4(w[4], w[5], w[6], w[7]);
@@ -494,7 +498,7 @@ __global__ __launch_bounds__(kSubLanes) void hash_tail_kernel(
       w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
     } else {
       const int cur = (int)(m - first < ((int64_t)1 << K) ? m - first : ((int64_t)1 << K));
-      fold_children(c, cur, m0, v0, K, lds, lane, w);
+      fold_children<false>(c, cur, m0, v0, K, lds, lane, w);
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) vals[lane * 8 + k] = w[k];

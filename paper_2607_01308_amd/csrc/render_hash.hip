@@ -73,7 +73,7 @@ __device__ __forceinline__ void compress_block(B3Cv& st, const u32x4 (&x)[4], ui
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int k = 0; k < 4; ++k) w[4 * q + k] = x[q][k];
-  b3_compress(st, w, chunk, 64, flags);
+  b3_compress_paired<0>(st, w, chunk, 64, flags);   // two waves per SIMD
 }
 
 // N consecutive (cos, sin) pairs j0 .. j0 + N - 1 of a slot's pair-ordered
