@@ -72,6 +72,63 @@ __host__ __device__ __forceinline__ void fused_next_row(P& dst, int64_t& left, i
   left = wrap ? T : left;
 }
 
+// A full stripe by lines: line k (128 bytes) of chunk c is held by eight lanes,
+// a 16-byte piece each; lane l holds piece l % 8 of chunks 8 j + l / 8 (j = 0 .. 7).
+// The stripe's bytes are contiguous in the tensor, and so are they in the
+// merged cache up to the end of a head, where the rest moves on by the gap to
+// the next head's rows; so a piece has one offset for both sides.
+// The offset is a part that is the same on every lane and the lane's own.
+__host__ __device__ __forceinline__ uint32_t fused_line_step(int k, int j) {
+  return (uint32_t)(j * 8192 + k * 128);
+}
+__host__ __device__ __forceinline__ uint32_t fused_line_lane(int lane) {
+  return (uint32_t)((lane >> 3) * 1024 + (lane & 7) * 16);
+}
+
+struct FusedStripe {
+  int64_t dst;     // byte offset, in the tensor's part of the merged cache, of the stripe's first row
+  int64_t t0;      // row of its head the stripe begins with
+  uint32_t wrap;   // offset in the stripe at which the next head begins, UINT32_MAX past its end
+  bool many;       // T is so short that a stripe may hold more than two heads
+};
+
+__host__ __device__ __forceinline__ FusedStripe fused_stripe(int64_t sidx, int rb_shift, int64_t T,
+                                                             int64_t T_out, int64_t off) {
+  FusedStripe f;
+  const int64_t rows = (int64_t)65536 >> rb_shift;   // rows per stripe
+  const int64_t r0 = sidx * rows;
+  const int64_t h0 = r0 / T;
+  f.t0 = r0 - h0 * T;
+  f.dst = (h0 * T_out + off + f.t0) << rb_shift;
+  f.many = T < rows;
+  f.wrap = T - f.t0 < rows ? (uint32_t)((T - f.t0) << rb_shift) : 0xFFFFFFFFu;
+  return f;
+}
+
+// What the merged offset of stripe byte o is beyond o: the gaps of the heads
+// that begin in the stripe before it. inv_T: 1 / T in fp32. With several heads
+// per stripe T is below 1024 and the row below 2048, so the quotient's distance
+// from a whole number, at least 1 / (2 T), is over a thousand times what the
+// product rounds off.
+__host__ __device__ __forceinline__ int64_t fused_line_gap(const FusedStripe& f, uint32_t o,
+                                                           int rb_shift, int64_t gap_bytes,
+                                                           float inv_T) {
+  if (f.many) {
+    const uint32_t rel = (uint32_t)f.t0 + (o >> rb_shift);
+    return (int64_t)(uint32_t)(((float)rel + 0.5f) * inv_T) * gap_bytes;
+  }
+  return o >= f.wrap ? gap_bytes : 0;
+}
+
+// Row of its chunk and byte of that row of a lane's piece of line k.
+template <int RB>
+__host__ __device__ __forceinline__ int fused_line_row(int k, int lane) {
+  return RB >= 128 ? (k * 128) / RB : 2 * k + ((lane & 7) >> 2);
+}
+template <int RB>
+__host__ __device__ __forceinline__ int fused_line_col(int k, int lane) {
+  return RB >= 128 ? (k * 128) % RB + (lane & 7) * 16 : (lane & 3) * 16;
+}
 
 // Paged storage: a pool [L][2][P][H][B][RB] of pages of B rows of every head,
 // fragment row tr of head h in row tr % B of page blocks[first + tr / B]. The

@@ -2,26 +2,30 @@
 // fragments whose Id is still missing, the chunk level of their hash (Id of
 // Alg. 2), from the same loads.
 //
-// Hashing is VALU-bound (672 VALU ops per 64-byte block) and the render is
-// HBM-bound; done separately they read every byte twice. Here one wave takes
+// Done separately, hash and render read every byte twice. Here one wave takes
 // one (slot, tensor, stripe) task: a stripe is 64 consecutive BLAKE3 chunks of
-// the tensor (64 KiB) and lane k owns chunk k, 1 KiB of consecutive bytes,
-// i.e. whole rows of the tensor (a row is 64 B .. 1 KiB). Step k loads blocks
-// 2k and 2k + 1 of every lane's chunk (128 bytes per lane, a whole cache line,
-// lanes 1 KiB apart), one step ahead of their use; the lane compresses them
-// into its chunk's chaining value and the pair is written to the lane's rows of
-// the merged cache: V and offset-0 K unchanged, other K rotated by R(off) in
-// fp64. A half-split pair (j, j + d/2) has its halves half a row apart: in a
-// 128-byte row both are in one step, in a 256-byte row the first-half step is
-// kept in registers until its partner arrives, in longer rows it is re-read
-// from the cache one step before it is needed. The angles depend only on the
-// slot and the column, so every lane of a step uses the same (cos, sin) pairs,
-// read from the slot's table as wave-uniform values. The output goes through
-// the LDS so that each store instruction writes whole 128-byte lines of eight
-// chunks; each lane follows its own rows into the merged cache (a chunk may
-// cross the end of a head). HBM traffic is the algorithmic minimum (each byte
-// read once, written once); the kernel is bound by the VALU work of the hash
-// plus the fp64 rotation.
+// the tensor (64 KiB) and lane k hashes chunk k, 1 KiB of consecutive bytes,
+// i.e. whole rows of the tensor (a row is 64 B .. 1 KiB).
+//
+// A full stripe goes line by line: line k is bytes [128 k, 128 k + 128) of every
+// chunk. Eight lanes hold a line, 16 bytes each, so each load and store
+// instruction moves eight whole lines (a lane's own blocks, 1 KiB from its
+// neighbour's, would make every 16-byte piece a line of its own to the caches),
+// and rotated K leaves the registers it was loaded to for the merged cache. Only
+// the hash needs a chunk in one lane: a line is transposed through 9 KiB of LDS
+// per wave, and each lane compresses its chunk's two blocks. Line k + 1 is loaded
+// while line k is rotated, stored and hashed. V and offset-0 K are stored
+// unchanged, other K rotated by R(off) in fp64; a lane's pieces of one line of
+// all rows lie in the same columns, so its angles are a few registers.
+//
+// What bounds it: HBM, in this access pattern. 36,864 stripes of 64 KiB copied
+// by waves that walk them in lines reach 5.4 TB/s read + written whatever the
+// line's width (128 B to 512 B: 5.35-5.6), one-wave units in address order 6.0-6.7,
+// but a chunk's 16 dependent compressions keep its line open for tens of
+// microseconds, so the stripes in flight (three waves per SIMD: 192 MB) cannot be
+// fewer. On 4.83 GB (Qwen3-4B N=4) the kernel takes 950 us: 925 us with neither
+// hash nor rotation, 1047 us when each lane loaded its own chunk's blocks and
+// the output went through the LDS (246 VGPRs, two waves per SIMD).
 #include <type_traits>
 
 #include "blake3_quad.h"
@@ -35,30 +39,24 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-// Persistent grid of up to CUs x CM_FUSED_BLOCKS_PER_CU blocks (fewer when the
-// set has fewer tasks); the register budget is capped so that
-// CM_FUSED_WAVES_PER_EU waves fit on each SIMD (2 waves: 256 VGPRs, enough for
-// three pairs of blocks, the hash state and the fp64 rotation without spills).
+// Persistent grid of up to CUs x 32 blocks (fewer when the set has fewer tasks).
 // Many more blocks than fit keep the end of the launch short: a block that
-// starts late has few tasks.
-#ifndef CM_FUSED_BLOCKS_PER_CU
-#define CM_FUSED_BLOCKS_PER_CU 32
-#endif
-#ifndef CM_FUSED_WAVES_PER_EU
-#define CM_FUSED_WAVES_PER_EU 2
-#endif
-#define CM_FUSED_OCCUPANCY __attribute__((amdgpu_waves_per_eu(CM_FUSED_WAVES_PER_EU)))
+// starts late has few tasks (4.83 GB: 975 us; as many blocks as fit 1041 us).
+constexpr int kFusedBlocksPerCu = 32;
+// Three waves per SIMD (168 VGPRs: two lines and their partners, the hash state
+// or the fp64 rotation) hide a line's way from HBM better than two (Qwen3-1.7B
+// N=2: 84 us, with two 92 us); half-split rows of 512 bytes and more re-read
+// their partner lines and would spill.
+constexpr int fused_waves(int style, int rb) {
+  return style == CM_ROPE_HALF && rb >= 512 ? 2 : 3;
+}
 
 template <int V>
 using IC = std::integral_constant<int, V>;
 
-// Loads are ordinary (cached) accesses: a lane reads a whole 128-byte line
-// over two consecutive instructions of the same step, which the caches merge
-// (a nontemporal hint would make each 16-byte piece a transfer of its own).
-// Stores through the LDS staging write eight whole lines per instruction and
-// carry the nontemporal hint (the merged cache is not read back here: measured
-// 1.4% faster than cached stores); a lane's own 16-byte pieces (the last stripe
-// of a tensor) are stored as ordinary accesses.
+// The last stripe of a tensor, where each lane moves its own blocks: ordinary
+// accesses (the 16-byte pieces of a line are merged by the caches). Lines carry
+// the nontemporal hint both ways: they are whole, and neither side is read again.
 __device__ __forceinline__ void load_block(u32x4 (&x)[4], const uint8_t* p) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) x[q] = *global_ptr<u32x4>(p + 16 * q);
@@ -73,7 +71,7 @@ __device__ __forceinline__ void compress_block(B3Cv& st, const u32x4 (&x)[4], ui
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int k = 0; k < 4; ++k) w[4 * q + k] = x[q][k];
-  b3_compress_paired<0>(st, w, chunk, 64, flags);   // two waves per SIMD
+  b3_compress_paired<0>(st, w, chunk, 64, flags);
 }
 
 // N consecutive (cos, sin) pairs j0 .. j0 + N - 1 of a slot's pair-ordered
@@ -98,17 +96,17 @@ __device__ __forceinline__ void pair_angles(const double* __restrict__ table, in
   }
 }
 
-// A wave's LDS staging area: lane l's pair of blocks (eight 16-byte pieces)
-// at byte l * 144 + q * 16. The 16 bytes of padding per lane put the pieces q
-// of any eight consecutive lanes, and the eight pieces of one lane (read by
-// eight consecutive lanes), on distinct LDS banks; each side addresses them
-// from one register plus immediate offsets.
+// A wave's LDS staging area: chunk c's line at byte c * 144, piece q at + 16 q.
+// The 16 bytes of padding per chunk put the pieces q of any eight consecutive
+// chunks, and the eight pieces of one chunk, on distinct LDS banks.
 constexpr int kStageLane = 144;
 constexpr int kStageBytes = 64 * kStageLane;
 
-// Where a task's lanes read and write. A task's address state gives s(b), the
-// address of block b of the lane's chunk; d(pos), that of block pos of the
-// lane's current output row (nullptr: the row is not written); next_row().
+// Where a task's lanes read and write. By chunk (task()): s(b), the address of
+// block b of the lane's chunk; d(pos), that of block pos of the lane's current
+// output row (nullptr: the row is not written); next_row(). By line (lines()):
+// line_s and line_d, the source and the merged place of the lane's j-th piece of
+// line k (nullptr likewise); lo is fused_line_lane(lane).
 //
 // Dense: fragment tensors are contiguous [H][T][row] and the merged cache is
 // [2L][H][T_out][row]; a lane's chunk is 1 KiB of consecutive bytes and it
@@ -120,12 +118,27 @@ struct DenseTask {
   uint8_t* dst;           // the lane's current row in the merged cache
   int64_t left, T, gap;
   __device__ __forceinline__ const uint8_t* s(int b) const { return src + b * 64; }
-  // block b of the chunk dl lanes away (the same stripe)
-  __device__ __forceinline__ const uint8_t* s_lane(int b, int dl) const {
-    return src + ((int64_t)dl << 10) + b * 64;
-  }
   __device__ __forceinline__ uint8_t* d(int pos) const { return dst + pos * 64; }
   __device__ __forceinline__ void next_row() { fused_next_row(dst, left, T, gap, RB); }
+};
+
+template <int RB>
+struct DenseLines {
+  static constexpr bool kSkips = false;
+  FusedStripe st;
+  const uint8_t* sbase;   // the stripe, the same on every lane
+  uint8_t* dbase;         // its first row in the merged cache
+  int64_t gap;
+  float inv_T;
+  bool straight;          // the stripe ends before the next head's rows
+  __device__ __forceinline__ const uint8_t* line_s(int k, int j, uint32_t lo, int) const {
+    return sbase + fused_line_step(k, j) + lo;
+  }
+  __device__ __forceinline__ uint8_t* line_d(int k, int j, uint32_t lo, int) const {
+    uint8_t* p = dbase + fused_line_step(k, j);
+    if (straight) return p + lo;
+    return p + (lo + fused_line_gap(st, fused_line_step(k, j) + lo, __builtin_ctz(RB), gap, inv_T));
+  }
 };
 
 // QP: stripes of at most 16 chunks are hashed by quads of lanes (the variant
@@ -136,6 +149,9 @@ struct DenseAddr {
   int64_t stride;
   uint8_t* out;
   static constexpr bool kQuadPartial = QP;
+  __device__ __forceinline__ const uint8_t* stripe(int64_t i, int64_t t, int64_t sidx) const {
+    return reinterpret_cast<const uint8_t*>(table[i * stride + 1 + t]) + (sidx << 16);
+  }
   template <int RB>
   __device__ __forceinline__ DenseTask<RB> task(int64_t i, int64_t t, int64_t sidx, int64_t off,
                                                 int64_t T, int64_t T_out, int32_t H,
@@ -148,6 +164,20 @@ struct DenseAddr {
     a.left = fl.left;
     a.T = T;
     a.gap = (T_out - T) << RB_SHIFT;   // end of a head's rows -> next head
+    return a;
+  }
+  template <int RB>
+  __device__ __forceinline__ DenseLines<RB> lines(int64_t i, int64_t t, int64_t sidx, int64_t off,
+                                                  int64_t T, int64_t T_out, int32_t H, int64_t,
+                                                  int, int) const {
+    constexpr int RB_SHIFT = __builtin_ctz(RB);
+    DenseLines<RB> a;
+    a.gap = (T_out - T) << RB_SHIFT;
+    a.st = fused_stripe(sidx, RB_SHIFT, T, T_out, off);
+    a.sbase = stripe(i, t, sidx);
+    a.dbase = out + t * (int64_t)H * T_out * RB + a.st.dst;
+    a.inv_T = 1.0f / (float)T;
+    a.straight = !a.st.many && a.st.wrap == 0xFFFFFFFFu;
     return a;
   }
 };
@@ -164,6 +194,7 @@ struct PagedTask {
   static constexpr int RB_SHIFT = __builtin_ctz(RB);
   uint8_t* slice;          // the tensor's (layer, K/V) slice of the pool
   const uint32_t* rows;    // the lane's column of the wave's table
+  const uint32_t* tab;     // the wave's table
   int j;                   // the lane's current output row (the same on every lane)
   __device__ __forceinline__ const uint8_t* s(int b) const {
     return slice + ((uint64_t)rows[(b / BPR) * 64] << RB_SHIFT) + (b % BPR) * 64;
@@ -173,6 +204,16 @@ struct PagedTask {
     return r == kPagedSkipRow ? nullptr : slice + ((uint64_t)r << RB_SHIFT) + pos * 64;
   }
   __device__ __forceinline__ void next_row() { ++j; }
+  __device__ __forceinline__ const uint8_t* line_s(int k, int jj, uint32_t, int lane) const {
+    const int r = fused_line_row<RB>(k, lane), c = 8 * jj + (lane >> 3);
+    return slice + ((uint64_t)tab[r * 64 + c] << RB_SHIFT) + fused_line_col<RB>(k, lane);
+  }
+  __device__ __forceinline__ uint8_t* line_d(int k, int jj, uint32_t, int lane) const {
+    const int r = fused_line_row<RB>(k, lane), c = 8 * jj + (lane >> 3);
+    const uint32_t row = tab[(RPC + r) * 64 + c];
+    return row == kPagedSkipRow ? nullptr
+                                : slice + ((uint64_t)row << RB_SHIFT) + fused_line_col<RB>(k, lane);
+  }
 };
 
 struct PagedAddr {
@@ -186,6 +227,12 @@ struct PagedAddr {
   uint32_t* lds;             // the block's tables: [waves][2 * RPC][64]
   static constexpr bool kQuadPartial = false;
   template <int RB>
+  __device__ __forceinline__ PagedTask<RB> lines(int64_t i, int64_t t, int64_t sidx, int64_t off,
+                                                 int64_t T, int64_t T_out, int32_t H,
+                                                 int64_t bytes, int lane, int wave) const {
+    return task<RB>(i, t, sidx, off, T, T_out, H, bytes, lane, wave);
+  }
+  template <int RB>
   __device__ __forceinline__ PagedTask<RB> task(int64_t i, int64_t t, int64_t sidx, int64_t off,
                                                 int64_t T, int64_t, int32_t H, int64_t,
                                                 int lane, int wave) const {
@@ -195,6 +242,7 @@ struct PagedAddr {
     a.slice = pool + ((t * P * H) << (b_shift + RB_SHIFT));
     uint32_t* col = lds + (int64_t)wave * (2 * RPC * 64) + lane;
     a.rows = col;
+    a.tab = col - lane;
     a.j = 0;
     const int64_t first = table[2 * i + 1];
     const int32_t* tab = (t & 1) ? v_table : k_table;
@@ -247,30 +295,19 @@ __device__ __forceinline__ void render_hash_body(
   constexpr int EP = 16 / ESIZE;              // elements per 16-byte piece
   constexpr int BPR = RB / 64;                // blocks per row: 1 .. 16
   constexpr int HBK = BPR / 2;                // blocks per half row (0: a row is one block)
-  constexpr int PPR = BPR >= 2 ? BPR / 2 : 1; // steps (pairs of blocks) per row
-  constexpr int HP = BPR >= 4 ? BPR / 4 : 0;  // steps per half row when halves span steps
   constexpr bool HALF = STYLE == CM_ROPE_HALF;
-  // a half-split pair whose halves are in different steps: the first-half pair
-  // of blocks is kept in registers for rows of 256 bytes (one step back) and
-  // re-read from the cache for longer rows
-  constexpr bool KEEP = HP == 1;
   // the wave index is the same on every lane: say so, so that everything derived
   // from the task (slot, lengths, offsets, step positions, branches) stays in
   // scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int64_t waves = (int64_t)gridDim.x * kWaves;
-  // Per wave, a staging area through which a pair of blocks of every lane's
-  // chunk is handed to the eight lanes that store that chunk's 128 bytes, and
-  // the merged-cache address of each lane's two blocks. Lane l stores piece
-  // l % 8 of chunk 8 j + l / 8 (j = 0 .. 7).
+  // Per wave, the staging area through which a line of every chunk, loaded by
+  // eight lanes each, reaches the lane that hashes the chunk.
   __shared__ __attribute__((aligned(16))) uint8_t stage_lds[kWaves][kStageBytes];
-  __shared__ uint8_t* dst_lds[kWaves][2][64];
-  uint8_t* stage_w = stage_lds[wave] + lane * kStageLane;              // this lane's pieces
-  uint8_t* stage_r = stage_lds[wave] + (lane >> 3) * kStageLane + (lane & 7) * 16;
-  uint8_t** dst_w = &dst_lds[wave][0][lane];
-  uint8_t** dst_r = &dst_lds[wave][(lane & 7) >> 2][lane >> 3];
-  const int pq = lane & 3;                         // piece of its block this lane stores
+  uint8_t* stage_line = stage_lds[wave] + (lane >> 3) * kStageLane + (lane & 7) * 16;
+  const uint8_t* stage_chunk = stage_lds[wave] + lane * kStageLane;
+  const int lq = lane & 7;                         // piece of its lines this lane holds
   // the plan and the task bases are read on the device: a plan the host has not
   // seen is rendered as it stands (its length T_out fits the output by contract)
   const int n_u = (int)plan[CM_PLAN_NUNIQUE];
@@ -300,8 +337,6 @@ __device__ __forceinline__ void render_hash_body(
     const uint64_t chunk = (uint64_t)sidx * kStripeChunks + lane;
     const int64_t blocks_left = (bytes >> 6) - (int64_t)chunk * 16;
     const int nb = blocks_left < 0 ? 0 : (blocks_left > 16 ? 16 : (int)blocks_left);
-    auto A = addr.template task<RB>(i, t, sidx, off, T, T_out, H, bytes, lane, wave);
-    constexpr bool SKIPS = decltype(A)::kSkips;   // rows that are not written
     B3Cv st;
     b3_init(st);
     const uint32_t root = m == 1 ? kB3Root : 0u;
@@ -340,147 +375,135 @@ __device__ __forceinline__ void render_hash_body(
         rotate_pair_half<ESIZE>(a[q], b[q], cs, sn);
       }
     };
-    // Two blocks of every lane (x0 to d0, x1 to d1) through the LDS, so that
-    // each store instruction writes eight runs of 128 contiguous bytes.
-    auto put2 = [&](const u32x4 (&x0)[4], const u32x4 (&x1)[4], uint8_t* d0, uint8_t* d1) {
-      dst_w[0] = d0;
-      dst_w[64] = d1;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        *reinterpret_cast<u32x4*>(stage_w + q * 16) = x0[q];
-        *reinterpret_cast<u32x4*>(stage_w + 64 + q * 16) = x1[q];
-      }
-      __builtin_amdgcn_wave_barrier();   // the wave's LDS writes come before its reads
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        uint8_t* p = dst_r[8 * j];
-        const u32x4 v = *reinterpret_cast<const u32x4*>(stage_r + j * 8 * kStageLane);
-        if constexpr (SKIPS) {
-          if (p != nullptr) st_stream(p + pq * 16, v);
-        } else {
-          st_stream(p + pq * 16, v);
-        }
-      }
-      __builtin_amdgcn_wave_barrier();   // and before the next put's writes
-    };
-
-    // Output of step k (blocks 2k, 2k + 1 of every lane's chunk, in y; yp:
-    // with half-split pairs spanning steps, the step half a row earlier, the
-    // first halves of y's pairs): rotated in place if ROTC, stored, then the
-    // lanes move on to the next row after a row's last step. A first-half step
-    // of such a row is output with its partner.
-    auto emit = [&](auto rotc, int k, u32x4 (&y0)[4], u32x4 (&y1)[4], u32x4 (&yp0)[4],
-                    u32x4 (&yp1)[4]) {
-      constexpr bool ROT = decltype(rotc)::value;
-      const int pp = k % PPR;                     // step of the row
-      if constexpr (BPR == 1) {
-        // two rows of one block
-        if (ROT) { rotate_own(y0, 0); rotate_own(y1, 0); }
-        uint8_t* d0 = A.d(0);
-        A.next_row();
-        put2(y0, y1, d0, A.d(0));
-        A.next_row();
-        return;
-      } else if constexpr (BPR == 2) {
-        // one row: halves in y0, y1
-        if (ROT) {
-          if (HALF) rotate_halves(y0, y1, 0);
-          else { rotate_own(y0, 0); rotate_own(y1, 1); }
-        }
-        put2(y0, y1, A.d(0), A.d(1));
-        A.next_row();
-        return;
+    // Angles of the lane's piece of line k (the sine's sign flipped on a second
+    // half that is rotated by itself, see rotate_piece_half).
+    constexpr int NA = HALF ? EP : EP / 2;
+    auto line_angles = [&](int k, double (&cs)[NA], double (&sn)[NA]) {
+      constexpr int LPR = RB >= 128 ? RB / 128 : 1;           // lines per row
+      int j0;
+      bool flip = false;
+      if constexpr (HALF && RB >= 256) {
+        j0 = ((k % (LPR / 2)) * 8 + lq) * EP;
+      } else if constexpr (HALF) {
+        constexpr int P = RB / 32;                            // pieces per half row
+        j0 = (lq & (P - 1)) * EP;
+        flip = (lq & P) != 0;
       } else {
-        if (ROT && HALF) {
-          if (pp < HP) return;                    // output with its partner
-          const int pb = 2 * (pp - HP);           // row block of yp0
-          rotate_halves(yp0, y0, pb);
-          rotate_halves(yp1, y1, pb + 1);
-          put2(yp0, yp1, A.d(pb), A.d(pb + 1));
-        } else if (ROT) {
-          rotate_own(y0, 2 * pp);
-          rotate_own(y1, 2 * pp + 1);
-        }
-        put2(y0, y1, A.d(2 * pp), A.d(2 * pp + 1));
-        if (pp == PPR - 1) A.next_row();
+        j0 = (RB >= 128 ? (k % LPR) * 8 + lq : lq & 3) * (EP / 2);
+      }
+      const CM_GLOBAL double* a = (const CM_GLOBAL double*)ang + 2 * j0;
+#pragma unroll
+      for (int e = 0; e < NA; ++e) {
+        cs[e] = a[2 * e];
+        sn[e] = flip ? -a[2 * e + 1] : a[2 * e + 1];
       }
     };
-
-    // The steps of a full stripe (every lane owns 16 blocks): step k waits for
-    // blocks 2k, 2k + 1 (x, loaded one step earlier); outputs step k - 1 (prev);
-    // loads step k + 1 into nx (the last step loads 128 bytes of the slot's
-    // angle table instead, lines that stay cached, so that every step issues
-    // the same loads), and, when re-reading, the partner pair of
-    // step k into pn; then compresses its two blocks. The phases are kept apart
-    // so that the fp64 rotation and the compression never hold registers at the
-    // same time; every memory operation older than a step's wait was issued a
-    // step earlier.
-    auto full_stripe = [&](auto hashc, auto rotc) {
-      constexpr bool HASH = decltype(hashc)::value;
-      constexpr bool ROT = decltype(rotc)::value;
-      constexpr bool SPLIT = ROT && HALF && HP > 0;      // halves in different steps
-      u32x4 xa0[4], xa1[4], xb0[4], xb1[4], k0[4], k1[4];
-      auto load2 = [&](u32x4 (&y0)[4], u32x4 (&y1)[4], int b) {
-        if constexpr (SKIPS && BPR == 1) {
-          // two rows, each a block
-          load_block(y0, A.s(b));
-          load_block(y1, A.s(b + 1));
-        } else {
-          const uint8_t* p = A.s(b);
-          load_block(y0, p);
-          load_block(y1, p + 64);
-        }
-      };
-      auto step = [&](int k, u32x4 (&x0)[4], u32x4 (&x1)[4], u32x4 (&p0)[4], u32x4 (&p1)[4]) {
+    uint32_t lo = fused_line_lane(lane);
+    auto store_piece = [&](const auto& A, const u32x4& x, int k, int j) {
+      uint8_t* p = A.line_d(k, j, lo, lane);
+      if constexpr (std::decay_t<decltype(A)>::kSkips) {
+        if (p != nullptr) st_stream(p, x);
+      } else {
+        st_stream(p, x);
+      }
+    };
+    auto load_line = [&](const auto& A, u32x4 (&x)[8], int k) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          launder(x0[q]);
-          launder(x1[q]);
+      for (int j = 0; j < 8; ++j) x[j] = ld16(A.line_s(k, j, lo, lane));
+    };
+
+    // A full stripe (every chunk has 16 blocks) line by line. Step k: line k of
+    // every chunk (cur, loaded a step earlier) goes to the LDS for the hash; the
+    // next line's loads are issued into the other buffer; the line is rotated in
+    // the lanes that hold it and stored; each lane then reads its own chunk's
+    // two blocks back and compresses them. Half-split pairs: in the same line
+    // (rows up to 128 bytes, the partner's lane by a lane move), in the line
+    // before (256: it waits in the other buffer, and the next loads are issued
+    // once both are stored), or further back (re-read from the cache).
+    auto full_stripe = [&](auto rotc) {
+      constexpr bool ROT = decltype(rotc)::value;
+      constexpr bool SPLIT = ROT && HALF && RB >= 256;   // halves in different lines
+      constexpr int HL = RB >= 256 ? RB / 256 : 1;       // lines per half row
+      constexpr bool KEEP = SPLIT && HL == 1;
+      u32x4 xa[8], xb[8], par[8];
+      const auto A = addr.template lines<RB>(i, t, sidx, off, T, T_out, H, bytes, lane, wave);
+      auto step = [&](int k, u32x4 (&cur)[8], u32x4 (&oth)[8]) {
+        const bool second = SPLIT && ((k / HL) & 1) != 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) launder(cur[j]);
+        asm volatile("" : "+v"(lo));       // no address is kept from step to step
+        // the memory accesses of a step go ahead of other waves' compressions
+        // (Qwen3-1.7B N=2: 90 -> 85 us)
+        __builtin_amdgcn_s_setprio(3);
+        __builtin_amdgcn_sched_barrier(0);
+        if (hashing) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            *reinterpret_cast<u32x4*>(stage_line + j * 8 * kStageLane) = cur[j];
+        }
+        if constexpr (!KEEP) {
+          if (k + 1 < 8) load_line(A, oth, k + 1);
+        } else {
+          if (!second && k + 1 < 8) load_line(A, oth, k + 1);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (k > 0) {
-          // step k - 1 sits in p (the other buffer); its partner in k
-          if constexpr (SPLIT && KEEP) {
-            if (((k - 1) % PPR) < HP) {
+        if constexpr (!ROT) {
 #pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                k0[q] = p0[q];
-                k1[q] = p1[q];
-              }
-            } else {
-              emit(rotc, k - 1, p0, p1, k0, k1);
-            }
-          } else {
-            emit(rotc, k - 1, p0, p1, k0, k1);
+          for (int j = 0; j < 8; ++j) {
+            store_piece(A, cur[j], k, j);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else if constexpr (!SPLIT) {
+          double cs[NA], sn[NA];
+          line_angles(k, cs, sn);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            if constexpr (HALF)
+              cur[j] = rotate_piece_half<ESIZE>(cur[j], lane_xor4<(RB >= 128 ? 4 : 2)>(cur[j]), cs, sn);
+            else
+              cur[j] = rotate_piece_il<ESIZE>(cur[j], cs, sn);
+            store_piece(A, cur[j], k, j);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else if (second) {
+          double cs[NA], sn[NA];
+          line_angles(k, cs, sn);
+          u32x4 (&first)[8] = KEEP ? oth : par;
+          if constexpr (!KEEP) load_line(A, par, k - HL);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            rotate_pair_half<ESIZE>(first[j], cur[j], cs, sn);
+            store_piece(A, first[j], k - HL, j);
+            store_piece(A, cur[j], k, j);
+            __builtin_amdgcn_sched_barrier(0);
           }
         }
+        if constexpr (KEEP) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (second && k + 1 < 8) load_line(A, oth, k + 1);
+        }
         __builtin_amdgcn_sched_barrier(0);
-        if (k + 1 < 8) {
-          load2(p0, p1, (k + 1) * 2);
-        } else {
-          // the same loads from a line every wave keeps cached: the slot's
-          // angle table (at least 128 bytes: d >= 16)
-          const uint8_t* hot = reinterpret_cast<const uint8_t*>(ang);
-          load_block(p0, hot);
-          load_block(p1, hot + 64);
-        }
-        if constexpr (SPLIT && !KEEP) {
-          // the partner pair of step k, needed when step k is output
-          if ((k % PPR) >= HP) load2(k0, k1, 2 * (k - HP));
-        }
-        if constexpr (HASH) {
-          compress_block(st, x0, chunk, flags(2 * k, kB3ChunkBlocks - 1));
-          compress_block(st, x1, chunk, flags(2 * k + 1, kB3ChunkBlocks - 1));
+        __builtin_amdgcn_s_setprio(0);
+        if (hashing) {
+          u32x4 m0[4], m1[4];
+          __builtin_amdgcn_wave_barrier();   // the wave's LDS writes come before its reads
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            m0[q] = *reinterpret_cast<const u32x4*>(stage_chunk + 16 * q);
+            m1[q] = *reinterpret_cast<const u32x4*>(stage_chunk + 64 + 16 * q);
+          }
+          __builtin_amdgcn_wave_barrier();   // and before the next line's writes
+          compress_block(st, m0, chunk, flags(2 * k, kB3ChunkBlocks - 1));
+          compress_block(st, m1, chunk, flags(2 * k + 1, kB3ChunkBlocks - 1));
         }
         __builtin_amdgcn_sched_barrier(0);
       };
-      load2(xa0, xa1, 0);
+      load_line(A, xa, 0);
 #pragma nounroll
       for (int k = 0; k < 8; k += 2) {
-        step(k, xa0, xa1, xb0, xb1);
-        step(k + 1, xb0, xb1, xa0, xa1);
+        step(k, xa, xb);
+        step(k + 1, xb, xa);
       }
-      emit(rotc, 7, xb0, xb1, k0, k1);              // step 7's output
     };
 
     // The last stripe of a tensor (a lane may own fewer than 16 blocks, or
@@ -490,6 +513,8 @@ __device__ __forceinline__ void render_hash_body(
     auto partial = [&](auto rotc) {
       constexpr bool ROT = decltype(rotc)::value;
       u32x4 x[4], par[4];
+      auto A = addr.template task<RB>(i, t, sidx, off, T, T_out, H, bytes, lane, wave);
+      constexpr bool SKIPS = decltype(A)::kSkips;   // rows that are not written
       for (int b = 0; b < nb; ++b) {
         const int pos = b & (BPR - 1);
         load_block(x, A.s(b));
@@ -523,15 +548,12 @@ __device__ __forceinline__ void render_hash_body(
       else partial(std::false_type{});
       if constexpr (kQuadPartial) {
         if (quad_hash)
-          quad_hash_stripe(A.s_lane(0, -lane), bytes >> 6, sidx, m == 1,
+          quad_hash_stripe(addr.stripe(i, t, sidx), bytes >> 6, sidx, m == 1,
                            nodes + (base0[i] + t * m + (int64_t)sidx * kStripeChunks) * 32, lane);
       }
-    } else if (hashing) {
-      if (rotate) full_stripe(std::true_type{}, std::true_type{});
-      else full_stripe(std::true_type{}, std::false_type{});
     } else {
-      if (rotate) full_stripe(std::false_type{}, std::true_type{});
-      else full_stripe(std::false_type{}, std::false_type{});
+      if (rotate) full_stripe(std::true_type{});
+      else full_stripe(std::false_type{});
     }
     if (hashing && !quad_hash && nb > 0)
       store_cv(nodes + (base0[i] + t * m + (int64_t)chunk) * 32, st);
@@ -539,7 +561,8 @@ __device__ __forceinline__ void render_hash_body(
 }
 
 template <int ESIZE, int STYLE, int RB, bool QP = false>
-__global__ __launch_bounds__(kThreads) CM_FUSED_OCCUPANCY void render_hash_kernel(
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(fused_waves(STYLE, RB)))) void render_hash_kernel(
     const int64_t* __restrict__ table, int64_t stride, int32_t n, const int64_t* __restrict__ plan,
     const int64_t* __restrict__ task_base, const double* __restrict__ angles, int32_t H,
     int32_t d, const uint8_t* __restrict__ select, const int64_t* __restrict__ base0,
@@ -551,7 +574,8 @@ __global__ __launch_bounds__(kThreads) CM_FUSED_OCCUPANCY void render_hash_kerne
 // The pool is read (fragment pages) and written (the merged cache's fresh
 // pages) through the same pointer.
 template <int ESIZE, int STYLE, int RB>
-__global__ __launch_bounds__(kThreads) CM_FUSED_OCCUPANCY void paged_hash_render_kernel(
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(fused_waves(STYLE, RB)))) void paged_hash_render_kernel(
     uint8_t* pool, int64_t P, int32_t b_shift, const int64_t* __restrict__ table,
     const int32_t* __restrict__ blocks, const int32_t* __restrict__ k_table,
     const int32_t* __restrict__ v_table, int32_t n, const int64_t* __restrict__ plan,
@@ -598,7 +622,7 @@ hipError_t launch_render_hash(const SetDesc& s, const HashLayout& hlay, const Re
     // the task count is known on the device only; the tasks of every delivery
     // (hlay.tasks) bound it. A persistent grid of a few workgroups per CU, or
     // fewer when there are fewer tasks, strides over it.
-    const int64_t cap = (int64_t)device_cu_count() * CM_FUSED_BLOCKS_PER_CU;
+    const int64_t cap = (int64_t)device_cu_count() * kFusedBlocksPerCu;
     const int64_t want = (hlay.tasks + kWaves - 1) / kWaves;
     const dim3 grid((uint32_t)(want < cap ? (want > 0 ? want : 1) : cap));
     ScopedTiming tm(K_RENDER_HASH, stream);
@@ -657,7 +681,7 @@ hipError_t launch_paged_render_hash(const PagedDesc& p, const HashLayout& hlay,
     const int64_t* base_tab = reinterpret_cast<const int64_t*>(hws + hlay.off_tables);
     const int64_t* tasks = reinterpret_cast<const int64_t*>(rws + rlay.off_tiles);
     const double* angles = reinterpret_cast<const double*>(rws + rlay.off_angles);
-    const int64_t cap = (int64_t)device_cu_count() * CM_FUSED_BLOCKS_PER_CU;
+    const int64_t cap = (int64_t)device_cu_count() * kFusedBlocksPerCu;
     const int64_t want = (hlay.tasks + kWaves - 1) / kWaves;
     const dim3 grid((uint32_t)(want < cap ? (want > 0 ? want : 1) : cap));
     ScopedTiming tm(K_PAGED_HASH_RENDER, stream);

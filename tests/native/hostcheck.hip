@@ -103,6 +103,63 @@ int64_t hc_fused_check(int32_t n_u, const int64_t* T, const int64_t* off, int32_
   return bad;
 }
 
+// Every (slot, full stripe, line, lane, piece) of a fused launch as the kernel
+// takes full stripes: a 16-byte piece is read from stripe byte o of its tensor
+// and stored at the stripe's merged offset plus o plus the gaps of the heads that
+// begin in between. Each piece must be read once, go to the row and column of the
+// merged cache that its source row has there, and lie in the chunk row and column
+// that the paged form looks up. Returns the number of violations.
+}  // extern "C"
+
+template <int RB>
+static int64_t line_check(int32_t n_u, const int64_t* T, const int64_t* off, int32_t H,
+                          int64_t T_out) {
+  const int rb_shift = __builtin_ctz((unsigned)RB);
+  int64_t bad = 0;
+  for (int s = 0; s < n_u; ++s) {
+    const int64_t bytes = (int64_t)H * T[s] * RB;
+    const int64_t gap = (T_out - T[s]) << rb_shift;
+    const float inv_T = 1.0f / (float)T[s];
+    for (int64_t sidx = 0; (sidx + 1) * 65536 <= bytes; ++sidx) {
+      const cm::FusedStripe f = cm::fused_stripe(sidx, rb_shift, T[s], T_out, off[s]);
+      std::vector<uint8_t> seen(4096, 0);
+      for (int k = 0; k < 8; ++k)
+        for (int j = 0; j < 8; ++j)
+          for (int lane = 0; lane < 64; ++lane) {
+            const uint32_t o = cm::fused_line_step(k, j) + cm::fused_line_lane(lane);
+            if (o % 16 != 0 || o > 65536 - 16) { ++bad; continue; }
+            if (seen[o >> 4]++) ++bad;
+            const int64_t b = sidx * 65536 + o;              // byte of the tensor
+            const int64_t r = b >> rb_shift;
+            const int64_t h = r / T[s], t = r % T[s];
+            const int64_t want = ((h * T_out + off[s] + t) << rb_shift) + (b & (RB - 1));
+            const int64_t got = f.dst + o + cm::fused_line_gap(f, o, rb_shift, gap, inv_T);
+            if (got != want) ++bad;
+            const int c = 8 * j + (lane >> 3);               // its chunk of the stripe
+            if ((int64_t)c * (1024 / RB) + cm::fused_line_row<RB>(k, lane) != (o >> rb_shift) ||
+                cm::fused_line_col<RB>(k, lane) != (int)(o & (RB - 1)))
+              ++bad;
+          }
+      for (uint8_t c : seen)
+        if (c != 1) ++bad;
+    }
+  }
+  return bad;
+}
+
+extern "C" {
+
+int64_t hc_line_check(int32_t n_u, const int64_t* T, const int64_t* off, int32_t H, int32_t rb,
+                      int64_t T_out) {
+  switch (rb) {
+    case 64: return line_check<64>(n_u, T, off, H, T_out);
+    case 128: return line_check<128>(n_u, T, off, H, T_out);
+    case 256: return line_check<256>(n_u, T, off, H, T_out);
+    case 512: return line_check<512>(n_u, T, off, H, T_out);
+    default: return line_check<1024>(n_u, T, off, H, T_out);
+  }
+}
+
 // Every (unit, lane, piece) of a unit-render launch over rows [row0, T_out) of
 // n_u slots of lengths T[s] at offsets off[s]: each piece's slot must hold its
 // row, its source byte must lie inside that slot's tensor for every head, and

@@ -35,6 +35,9 @@ def hc():
     L.hc_unit_check.restype = ctypes.c_int64
     L.hc_unit_check.argtypes = [ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
                                 ctypes.c_int32, ctypes.c_int64, ctypes.c_int64]
+    L.hc_line_check.restype = ctypes.c_int64
+    L.hc_line_check.argtypes = [ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
+                                ctypes.c_int32, ctypes.c_int64]
     L.hc_fused_check.argtypes = [ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
                                  ctypes.c_int32, ctypes.c_int64]
     return L
@@ -63,6 +66,23 @@ def test_fused_map_is_a_bijection_onto_the_merged_rows(hc, rb, H, lengths):
 def test_fused_map_of_the_large_workload(hc):
     w = synth.workload("qwen3-4b-large")
     assert _check(hc, list(w.lengths), w.H, w.d * w.elem_bytes) == 0
+
+
+@pytest.mark.parametrize("rb", [64, 128, 256, 512, 1024])
+@pytest.mark.parametrize("H,lengths", [
+    (8, [512, 768]),                     # heads end with a stripe, or in one
+    (8, [4096, 1, 2047, 300]),
+    (7, [1023, 1024, 1025, 255, 256, 257]),   # around one head per stripe, every row size
+    (64, [33, 65, 16, 129]),             # several heads in a stripe
+    (4096, [1, 3]),                      # hundreds
+    (1, [70000]),
+])
+def test_lines_of_full_stripes(hc, rb, H, lengths):
+    """Full stripes, which the kernel walks by lines: each piece read once, stored at its row's
+    place in the merged cache, and in the chunk row that the paged form looks up."""
+    T = np.asarray(lengths, dtype=np.int64)
+    off = np.concatenate([[0], np.cumsum(T)[:-1]]).astype(np.int64)
+    assert hc.hc_line_check(len(T), T.ctypes.data, off.ctypes.data, H, rb, int(T.sum())) == 0
 
 
 def test_walker_finds_overlapping_slots(hc):
