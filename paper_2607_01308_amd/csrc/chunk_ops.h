@@ -1,5 +1,5 @@
 // Device helpers of the hash kernels (hash.hip, render_hash.hip): 64-byte block
-// loads, chaining-value stores, and the BLAKE3 chunk of one lane of a stripe.
+// loads and the BLAKE3 chunk of one lane of a stripe.
 #pragma once
 
 #include "blake3.h"
@@ -23,12 +23,6 @@ __device__ __forceinline__ void load_block64(const uint8_t* p, uint32_t (&m)[16]
     m[4 * k + 2] = v[2];
     m[4 * k + 3] = v[3];
   }
-}
-
-__device__ __forceinline__ void store_cv(uint8_t* out, const B3Cv& s) {
-  uint4* q = reinterpret_cast<uint4*>(out);
-  q[0] = make_uint4(s.h[0], s.h[1], s.h[2], s.h[3]);
-  q[1] = make_uint4(s.h[4], s.h[5], s.h[6], s.h[7]);
 }
 
 // Chunk `lane` of a stripe: `stripe` points at the stripe's first byte,

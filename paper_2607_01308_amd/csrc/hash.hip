@@ -7,18 +7,23 @@
 // dependent compressions, each 64-byte block loaded as four 16-byte pieces (the
 // lanes' loads are 1 KiB apart, so each lane reads whole 64-byte halves of
 // cache lines and the other half one block later), two blocks ahead of the
-// compression. The work is VALU-bound (12 VALU ops per G step, 672 per block);
-// the tree above the chunks takes one launch per three levels over all tensors
-// at full lane occupancy (the parents add 1/16 of the chunk work) until at most
-// nine levels remain, then one launch folds the top of every tensor's tree (and,
-// for a small set, computes each fragment's Id in its last workgroup; otherwise
-// one more launch does). Fragments stored in a page pool are hashed by a chunk
+// compression. The wave then folds its stripe's 64 chaining values through LDS
+// (stripe_fold.h), so a tensor's tree starts with two nodes per 64 KiB, or eight
+// on the largest sets, whose next three levels take one launch over all tensors
+// at full lane occupancy (as do tensors beyond 16 MiB in smaller sets); one launch
+// folds the top, at most nine levels, of every tensor's tree (and, for a small
+// set, computes each fragment's Id in its last workgroup; otherwise one more
+// launch does). Before the stripes were folded in the wave, a launch per three
+// levels read and wrote every chunk's value: 586 + 81 us after the fused kernel on
+// the Qwen3-4B large set, 16 us of the 150 on Qwen3-1.7B N=2. The chunks are bound by
+// the VALU (672 instructions per block) up to about 4.2 TB/s, where HBM reads in
+// this pattern are. Fragments stored in a page pool are hashed by a chunk
 // kernel that walks each chunk's blocks through the page list in the order of
 // the dense layout, so the Id does not depend on the storage.
-#include "blake3_quad.h"
 #include "chunk_ops.h"
 #include "key_mask.h"
 #include "knorm_fold.h"
+#include "stripe_fold.h"
 
 namespace cm {
 
@@ -120,12 +125,14 @@ __global__ __launch_bounds__(1024) void mask_hash_prep_kernel(
 __global__ __launch_bounds__(kBlock) void hash_chunk_kernel(const int64_t* __restrict__ table,
                                                             int32_t n, int64_t stride,
                                                             int64_t token_bytes,
-                                                            const int64_t* __restrict__ base0,
+                                                            int32_t level,
+                                                            const int64_t* __restrict__ base_v,
                                                             const int64_t* __restrict__ task_base,
                                                             int64_t total_tasks,
                                                             const uint8_t* __restrict__ select,
                                                             uint32_t want,
                                                             uint8_t* __restrict__ nodes) {
+  __shared__ __attribute__((aligned(16))) uint32_t fold_lds[kBlock / 64][kStripeChunks * 8];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wave
   const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
@@ -144,10 +151,13 @@ __global__ __launch_bounds__(kBlock) void hash_chunk_kernel(const int64_t* __res
     const uint8_t* p = reinterpret_cast<const uint8_t*>(table[(int64_t)i * stride + 1 + t]) +
                        ((sidx * kStripeBlocks) << 6);
     B3Cv s;
-    if (!hash_lane_chunk(s, p, in_stripe < kStripeBlocks ? in_stripe : kStripeBlocks, lane,
-                         chunk0, m == 1))
-      continue;
-    store_cv(nodes + (base0[i] + t * m + (int64_t)chunk0 + lane) * 32, s);
+    hash_lane_chunk(s, p, in_stripe < kStripeBlocks ? in_stripe : kStripeBlocks, lane, chunk0,
+                    m == 1);
+    const int64_t left = m - (int64_t)chunk0;
+    put_cv(fold_lds[wave], s, lane);
+    stripe_nodes<kChunkLevels>(fold_lds[wave], (int)(left < 64 ? left : 64), level, stripes == 1,
+                               lane, nodes + (base_v[i] + t * nodes_at(m, level) +
+                                              ((sidx * kStripeChunks) >> level)) * 32);
   }
 }
 
@@ -160,9 +170,11 @@ __global__ __launch_bounds__(kBlock) void hash_chunk_kernel(const int64_t* __res
 __global__ __launch_bounds__(kBlock) void paged_hash_chunk_kernel(
     const uint8_t* __restrict__ pool, int64_t P, int32_t H, int32_t b_shift, int32_t rb_shift,
     const int64_t* __restrict__ table, const int32_t* __restrict__ blocks, int32_t n,
-    int64_t token_bytes, const int64_t* __restrict__ base0, const int64_t* __restrict__ task_base,
+    int64_t token_bytes, int32_t level, const int64_t* __restrict__ base_v,
+    const int64_t* __restrict__ task_base,
     int64_t total_tasks, const uint8_t* __restrict__ select, uint32_t want,
     uint8_t* __restrict__ nodes) {
+  __shared__ __attribute__((aligned(16))) uint32_t fold_lds[kBlock / 64][kStripeChunks * 8];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wave
   const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
@@ -183,8 +195,8 @@ __global__ __launch_bounds__(kBlock) void paged_hash_chunk_kernel(
     const int64_t in_stripe = (bytes >> 6) - sidx * kStripeBlocks;
     const int64_t stripe_blocks = in_stripe < kStripeBlocks ? in_stripe : kStripeBlocks;
     const int64_t b0 = (int64_t)lane * kB3ChunkBlocks;
-    if (b0 >= stripe_blocks) continue;                 // lane past the tensor's last chunk
-    const int64_t nb = stripe_blocks - b0 < kB3ChunkBlocks ? stripe_blocks - b0 : kB3ChunkBlocks;
+    const bool has = b0 < stripe_blocks;               // a lane past the tensor's last chunk has none
+    const int64_t nb = !has ? 0 : stripe_blocks - b0 < kB3ChunkBlocks ? stripe_blocks - b0 : kB3ChunkBlocks;
     const int64_t c = sidx * kStripeChunks + lane;     // chunk index in the tensor
     // dense byte 1024 c = head h, row tr, column col
     const int64_t o = c << 10;
@@ -207,8 +219,12 @@ __global__ __launch_bounds__(kBlock) void paged_hash_chunk_kernel(
       }
     };
     B3Cv st;
-    b3_chunk<kChunkLevels>(st, nb, (uint64_t)c, m == 1, load);
-    store_cv(nodes + (base0[i] + t * m + c) * 32, st);
+    if (has) b3_chunk<kChunkLevels>(st, nb, (uint64_t)c, m == 1, load);
+    const int64_t left = m - sidx * kStripeChunks;
+    put_cv(fold_lds[wave], st, lane);
+    stripe_nodes<kChunkLevels>(fold_lds[wave], (int)(left < 64 ? left : 64), level, stripes == 1,
+                               lane, nodes + (base_v[i] + t * nodes_at(m, level) +
+                                              ((sidx * kStripeChunks) >> level)) * 32);
   }
 }
 
@@ -308,71 +324,6 @@ __global__ __launch_bounds__(kSubLanes) void hash_subtree_kernel(
   o[1] = make_uint4(w[4], w[5], w[6], w[7]);
 }
 
-// Fold cnt (>= 1) chaining values held in LDS (word w of value p at
-// [p * 8 + w][lane slot], lds_w words apart per value) into one, level by level:
-// value j of a level is the BLAKE3 parent of values 2j and 2j+1 of the level
-// below, an unpaired last value is carried up. ROOT marks the final compression
-// when root is set. All 64 lanes of the (one-wave) workgroup take part. A level
-// of at most 16 values is made by quads (b3_compress_quad: value j by lanes
-// 4j .. 4j + 3), which shortens the chain of dependent compressions about 2x;
-// a wider level takes one lane per value.
-__device__ __forceinline__ void fold_cvs(uint32_t* lds, int cnt, bool root, int lane) {
-  const int Q = lane >> 2;
-  const int q = lane & 3;
-  while (cnt > 1) {
-    const int nn = (cnt + 1) >> 1;
-    const uint32_t flags = kB3Parent | (root && nn == 1 ? kB3Root : 0u);
-    if (nn <= 16) {
-      uint32_t m[16];
-      uint32_t lo = 0, hi = 0;
-      const bool pair = Q < nn && 2 * Q + 1 < cnt;   // uniform over the quad
-      if (pair) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) m[k] = lds[(2 * Q) * 8 + k];
-      } else if (Q < nn) {
-        lo = lds[(2 * Q) * 8 + q];
-        hi = lds[(2 * Q) * 8 + 4 + q];
-      }
-      __syncthreads();
-      if (pair) {
-        b3_init_quad(lo, hi, (q & 1) != 0, (q & 2) != 0);
-        b3_compress_quad(lo, hi, m, 0, 64, flags, (q & 1) != 0, (q & 2) != 0);
-      }
-      if (Q < nn) {
-        lds[Q * 8 + q] = lo;
-        lds[Q * 8 + 4 + q] = hi;
-      }
-      __syncthreads();
-      cnt = nn;
-      continue;
-    }
-    uint32_t m[16];
-    const bool pair = lane < nn && 2 * lane + 1 < cnt;
-    const bool copy = lane < nn && 2 * lane + 1 >= cnt;
-    if (lane < nn) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) m[k] = lds[(2 * lane) * 8 + k];
-      if (pair) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) m[8 + k] = lds[(2 * lane + 1) * 8 + k];
-      }
-    }
-    __syncthreads();
-    if (pair) {
-      B3Cv cv;
-      b3_init(cv);
-      b3_compress(cv, m, 0, 64, flags);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) lds[lane * 8 + k] = cv.h[k];
-    } else if (copy) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) lds[lane * 8 + k] = m[k];
-    }
-    __syncthreads();
-    cnt = nn;
-  }
-}
-
 // Id = BLAKE3-256(header || root(K^0) || root(V^0) || ...) of fragment i by
 // one 64-lane workgroup. The message is L + 1 blocks (the header, then per
 // layer the pair of roots K, V) in C = ceil((L + 1) / 16) chunks. Lane k hashes
@@ -391,8 +342,8 @@ struct IdShape {
 __device__ __forceinline__ void fragment_id(uint64_t T, const IdShape& sh,
                                             const uint8_t* __restrict__ r,
                                             uint8_t* __restrict__ digest, int lane) {
-  __shared__ uint32_t chunk_cv[64 * 8];
-  __shared__ uint32_t group_cv[kFinalGroups * 8];
+  __shared__ __attribute__((aligned(16))) uint32_t chunk_cv[64 * 8];
+  __shared__ __attribute__((aligned(16))) uint32_t group_cv[kFinalGroups * 8];
   const int64_t blocks = (int64_t)sh.L + 1;
   const int64_t chunks = (blocks + kB3ChunkBlocks - 1) / kB3ChunkBlocks;
   const int groups = (int)((chunks + 63) / 64);
@@ -423,7 +374,7 @@ __device__ __forceinline__ void fragment_id(uint64_t T, const IdShape& sh,
       chunk_cv[Q * 8 + 4 + q] = hi;
     }
     __syncthreads();
-    fold_cvs(chunk_cv, (int)chunks, true, lane);
+    fold_cvs<-1>(chunk_cv, (int)chunks, true, lane);
     if (lane < 8) reinterpret_cast<uint32_t*>(digest)[lane] = chunk_cv[lane];
     return;
   }
@@ -440,11 +391,11 @@ __device__ __forceinline__ void fragment_id(uint64_t T, const IdShape& sh,
       for (int k = 0; k < 8; ++k) chunk_cv[lane * 8 + k] = cv.h[k];
     }
     __syncthreads();
-    fold_cvs(chunk_cv, cnt, groups == 1, lane);
+    fold_cvs<-1>(chunk_cv, cnt, groups == 1, lane);
     if (lane < 8) group_cv[g * 8 + lane] = chunk_cv[lane];
     __syncthreads();
   }
-  fold_cvs(group_cv, groups, true, lane);
+  fold_cvs<-1>(group_cv, groups, true, lane);
   if (lane < 8) reinterpret_cast<uint32_t*>(digest)[lane] = group_cv[lane];
 }
 
@@ -476,7 +427,7 @@ __global__ __launch_bounds__(kSubLanes) void hash_tail_kernel(
     const uint8_t* __restrict__ select, uint32_t want, const uint8_t* __restrict__ in,
     uint8_t* out, IdShape sh, int32_t* __restrict__ arrived, uint8_t* __restrict__ digests) {
   __shared__ uint32_t lds[(1 << (kSubLevels - 1)) * 8][kSubLanes];
-  __shared__ uint32_t vals[kSubLanes * 8];
+  __shared__ __attribute__((aligned(16))) uint32_t vals[kSubLanes * 8];
   __shared__ int32_t seen;
   const int t = blockIdx.x;
   const int i = blockIdx.y;
@@ -504,7 +455,7 @@ __global__ __launch_bounds__(kSubLanes) void hash_tail_kernel(
     for (int k = 0; k < 8; ++k) vals[lane * 8 + k] = w[k];
   }
   __syncthreads();
-  fold_cvs(vals, cnt, true, lane);
+  fold_cvs<-1>(vals, cnt, true, lane);
   if (lane < 8) reinterpret_cast<uint32_t*>(out + (base_top[i] + t) * 32)[lane] = vals[lane];
   if (!arrived) return;                  // the Ids come from hash_final_kernel
   __threadfence();                       // release this root to the other workgroups
@@ -532,6 +483,8 @@ __global__ __launch_bounds__(64) void hash_final_kernel(
 
 }  // namespace
 
+constexpr int64_t kFoldAllStripes = 131072;
+
 HashLayout hash_layout(const SetDesc& s) {
   HashLayout lay{};
   int64_t max_m0 = 1;
@@ -543,6 +496,13 @@ HashLayout hash_layout(const SetDesc& s) {
     lay.total1 += 2 * (int64_t)s.L * nodes_at(m0, 1);
   }
   while (((int64_t)1 << lay.levels) < max_m0) ++lay.levels;
+  // How far a wave folds its stripe. Stripes that are whole tensors: to the root
+  // (no launch between the chunks and the Id). Otherwise to two nodes: the sixth
+  // level would make one parent with the whole wave. From some 8 GiB of tensors on
+  // waves are never idle, and the upper levels, which use a part of the lanes, are
+  // left to a launch that uses all (level 3 against 5: Qwen3-4B large 16.12 against
+  // 16.29 ms, Qwen3-4B N=4 with 2.4 GB 1.124 against 1.109 ms).
+  lay.stripe_level = lay.levels <= 6 ? lay.levels : lay.tasks > kFoldAllStripes ? 3 : 5;
   if (lay.levels == 0) lay.total1 = 0;
   size_t off = 0;
   lay.off_tables = off;
@@ -572,13 +532,15 @@ hipError_t launch_hash_prep(const SetDesc& s, const HashLayout& lay, uint8_t* ws
 hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8_t* select,
                             uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream) {
   int64_t* base = reinterpret_cast<int64_t*>(ws + lay.off_tables);
-  // level 0 is in buf0; each launch reads one buffer and writes the other
-  // (buf1 holds every level it receives: they are no larger than level 1)
+  // the stripes' values are in buf0; each launch reads one buffer and writes the other
   uint8_t* buf[2] = {ws + lay.off_buf0, ws + lay.off_buf1};
   const int64_t nb1 = s.n + 1;
   hipError_t e = hipSuccess;
   int launch = 0;
-  int v0 = 0;
+  int v0 = lay.stripe_level;
+  // where the chunk kernels' stripes are whole tensors, the Ids' launch is all
+  // that is left of the trees, and is timed as such
+  const int id_timer = lay.levels > 0 && v0 == lay.levels ? K_HASH_PARENT : K_HASH_FINAL;
   // three levels per launch over all tensors while more than kTailLevels remain
   // (every tensor then has at most 2^kTailLevels nodes), then the rest at once
   for (; lay.levels - v0 > kTailLevels; v0 += kSubLevels, ++launch) {
@@ -611,7 +573,7 @@ hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8
     if ((e = hipGetLastError()) != hipSuccess || fuse_id) return e;
     ++launch;
   }
-  ScopedTiming tm(K_HASH_FINAL, stream);
+  ScopedTiming tm(id_timer, stream);
   hipLaunchKernelGGL(hash_final_kernel, dim3((uint32_t)s.n), dim3(64), 0, stream, s.table_dev,
                      s.stride, sh, base + lay.levels * nb1, select, want, buf[launch & 1],
                      digests);
@@ -648,7 +610,8 @@ hipError_t launch_hash(const SetDesc& s, const HashLayout& lay, const uint8_t* s
     const int64_t cap = (int64_t)device_cu_count() * kLeafBlocksPerCu;
     const int64_t grid = full < cap ? full : cap;
     hipLaunchKernelGGL(hash_chunk_kernel, dim3((uint32_t)grid), dim3(kBlock), 0, stream,
-                       s.table_dev, s.n, s.stride, token_bytes_of(s), base,
+                       s.table_dev, s.n, s.stride, token_bytes_of(s), lay.stripe_level,
+                       base + lay.stripe_level * nb1,
                        base + (int64_t)(lay.levels + 1) * nb1, lay.tasks, select, want,
                        ws + lay.off_buf0);
   }
@@ -673,7 +636,8 @@ hipError_t launch_hash_paged(const PagedDesc& p, const HashLayout& lay, const ui
     hipLaunchKernelGGL(paged_hash_chunk_kernel, dim3((uint32_t)grid), dim3(kBlock), 0, stream,
                        static_cast<const uint8_t*>(p.pool), p.pages, s.H, p.b_shift,
                        (int32_t)__builtin_ctzll((unsigned long long)s.row_bytes), s.table_dev,
-                       p.blocks_dev, s.n, token_bytes_of(s), base,
+                       p.blocks_dev, s.n, token_bytes_of(s), lay.stripe_level,
+                       base + lay.stripe_level * nb1,
                        base + (int64_t)(lay.levels + 1) * nb1, lay.tasks, select, want,
                        ws + lay.off_buf0);
   }

@@ -74,13 +74,14 @@ int device_cu_count();
 // an unpaired last node carried up, which is BLAKE3's left-balanced tree).
 struct HashLayout {
   int32_t levels;         // parent levels above the chunks (0 if every tensor is one chunk)
+  int32_t stripe_level;   // level of the nodes that the chunk kernels and the fused render write
   int64_t tasks;          // (tensor, stripe) work items of the chunk kernel
   int64_t total0;         // nodes at level 0 over all tensors
   int64_t total1;         // nodes at level 1 over all tensors (0 if levels == 0)
   size_t off_tables;      // int64 [levels+2][n+1]: per-level node bases, then task bases
   size_t off_arrived;     // int32 [n]: roots written per fragment (the tail kernel's Id step)
-  size_t off_buf0;        // level-0 (and even levels) node digests
-  size_t off_buf1;        // odd levels
+  size_t off_buf0;        // the stripes' nodes, and every second level launched after them
+  size_t off_buf1;        // the other levels
   size_t bytes;           // total workspace bytes
 };
 HashLayout hash_layout(const SetDesc& s);

@@ -28,10 +28,10 @@
 // the output went through the LDS (246 VGPRs, two waves per SIMD).
 #include <type_traits>
 
-#include "blake3_quad.h"
 #include "chunk_ops.h"
 #include "fused_geometry.h"
 #include "rotate.h"
+#include "stripe_fold.h"
 
 namespace cm {
 
@@ -265,23 +265,20 @@ struct PagedAddr {
 // quads of lanes: lanes 4Q .. 4Q + 3 hash chunk Q (b3_chunk_quad), a chain of
 // about half the latency of one lane's. On a small set such stripes are all the
 // work and few waves run. stripe: the stripe's first byte; blocks: the tensor's
-// 64-byte blocks; cvs: the stripe's first chaining value. Out of line: inlined,
-// it makes the 256-byte-row kernel spill.
-__device__ __attribute__((noinline)) void quad_hash_stripe(const uint8_t* stripe, int64_t blocks,
-                                                           int64_t sidx, bool root, uint8_t* cvs,
-                                                           int lane) {
+// 64-byte blocks. Returns words q and 4 + q of chunk Q's value in lane 4Q + q. Out
+// of line: inlined, it makes the 256-byte-row kernel spill.
+__device__ __attribute__((noinline)) uint2 quad_hash_stripe(const uint8_t* stripe, int64_t blocks,
+                                                            int64_t sidx, bool root, int lane) {
   const int Q = lane >> 2;
   const int64_t left = blocks - (sidx * kStripeChunks + Q) * 16;
   const int nb = left <= 0 ? 0 : (left > 16 ? 16 : (int)left);
-  if (nb == 0) return;                                 // uniform over the quad
+  uint32_t lo = 0, hi = 0;
   const uint8_t* c = stripe + ((int64_t)Q << 10);
-  uint32_t lo, hi;
-  b3_chunk_quad(lo, hi, nb, (uint64_t)(sidx * kStripeChunks + Q), root, (lane & 1) != 0,
-                (lane & 2) != 0,
-                [&](int64_t b, uint32_t (&w)[16]) { load_block64(c + b * 64, w); });
-  uint32_t* o = reinterpret_cast<uint32_t*>(cvs + (int64_t)Q * 32);
-  o[lane & 3] = lo;
-  o[4 + (lane & 3)] = hi;
+  if (nb != 0)                                         // uniform over the quad
+    b3_chunk_quad(lo, hi, nb, (uint64_t)(sidx * kStripeChunks + Q), root, (lane & 1) != 0,
+                  (lane & 2) != 0,
+                  [&](int64_t b, uint32_t (&w)[16]) { load_block64(c + b * 64, w); });
+  return make_uint2(lo, hi);
 }
 
 // ESIZE: element bytes; STYLE: pairing; RB: row bytes (64 .. 1024); Addr: the
@@ -290,7 +287,8 @@ template <int ESIZE, int STYLE, int RB, class Addr>
 __device__ __forceinline__ void render_hash_body(
     const Addr& addr, int32_t n, const int64_t* __restrict__ plan,
     const int64_t* __restrict__ task_base, const double* __restrict__ angles, int32_t H,
-    int32_t d, const uint8_t* __restrict__ select, const int64_t* __restrict__ base0,
+    int32_t d, const uint8_t* __restrict__ select, int32_t level,
+    const int64_t* __restrict__ base_v,
     uint8_t* __restrict__ nodes) {
   constexpr int EP = 16 / ESIZE;              // elements per 16-byte piece
   constexpr int BPR = RB / 64;                // blocks per row: 1 .. 16
@@ -546,17 +544,27 @@ __device__ __forceinline__ void render_hash_body(
     if (!full) {
       if (rotate) partial(std::true_type{});
       else partial(std::false_type{});
-      if constexpr (kQuadPartial) {
-        if (quad_hash)
-          quad_hash_stripe(addr.stripe(i, t, sidx), bytes >> 6, sidx, m == 1,
-                           nodes + (base0[i] + t * m + (int64_t)sidx * kStripeChunks) * 32, lane);
-      }
     } else {
       if (rotate) full_stripe(std::true_type{});
       else full_stripe(std::false_type{});
     }
-    if (hashing && !quad_hash && nb > 0)
-      store_cv(nodes + (base0[i] + t * m + (int64_t)chunk) * 32, st);
+    if (hashing) {
+      const int64_t left = m - sidx * kStripeChunks;
+      const int cnt = (int)(left < kStripeChunks ? left : kStripeChunks);
+      uint32_t* fold = reinterpret_cast<uint32_t*>(stage_lds[wave]);
+      if constexpr (kQuadPartial) {
+        if (quad_hash) {
+          const uint2 w = quad_hash_stripe(addr.stripe(i, t, sidx), bytes >> 6, sidx, m == 1, lane);
+          fold[(lane >> 2) * 8 + (lane & 3)] = w.x;
+          fold[(lane >> 2) * 8 + 4 + (lane & 3)] = w.y;
+        }
+      }
+      if (!quad_hash) put_cv(fold, st, lane);
+      stripe_nodes<0>(fold, cnt, level, stripes == 1, lane,
+                      nodes + (base_v[i] + t * nodes_at(m, level) +
+                               ((sidx * kStripeChunks) >> level)) * 32);
+      wave_lds_order();                  // the next task's lines go to the same LDS
+    }
   }
 }
 
@@ -565,10 +573,11 @@ __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(fused_waves(STYLE, RB)))) void render_hash_kernel(
     const int64_t* __restrict__ table, int64_t stride, int32_t n, const int64_t* __restrict__ plan,
     const int64_t* __restrict__ task_base, const double* __restrict__ angles, int32_t H,
-    int32_t d, const uint8_t* __restrict__ select, const int64_t* __restrict__ base0,
+    int32_t d, const uint8_t* __restrict__ select, int32_t level,
+    const int64_t* __restrict__ base_v,
     uint8_t* __restrict__ nodes, uint8_t* __restrict__ out) {
   render_hash_body<ESIZE, STYLE, RB>(DenseAddr<QP>{table, stride, out}, n, plan, task_base,
-                                     angles, H, d, select, base0, nodes);
+                                     angles, H, d, select, level, base_v, nodes);
 }
 
 // The pool is read (fragment pages) and written (the merged cache's fresh
@@ -580,12 +589,13 @@ __attribute__((amdgpu_waves_per_eu(fused_waves(STYLE, RB)))) void paged_hash_ren
     const int32_t* __restrict__ blocks, const int32_t* __restrict__ k_table,
     const int32_t* __restrict__ v_table, int32_t n, const int64_t* __restrict__ plan,
     const int64_t* __restrict__ task_base, const double* __restrict__ angles, int32_t H,
-    int32_t d, const uint8_t* __restrict__ select, const int64_t* __restrict__ base0,
+    int32_t d, const uint8_t* __restrict__ select, int32_t level,
+    const int64_t* __restrict__ base_v,
     uint8_t* __restrict__ nodes) {
   __shared__ uint32_t rows_lds[kWaves * 2 * (1024 / RB) * 64];
   render_hash_body<ESIZE, STYLE, RB>(
       PagedAddr{pool, P, b_shift, table, blocks, k_table, v_table, rows_lds}, n, plan, task_base,
-      angles, H, d, select, base0, nodes);
+      angles, H, d, select, level, base_v, nodes);
 }
 
 // Calls go(IC<RB>) for the row size of the set.
@@ -616,7 +626,8 @@ hipError_t launch_render_hash(const SetDesc& s, const HashLayout& hlay, const Re
     return e;
   const uint8_t* hsel = rws + rlay.off_hsel;  // 0: slot delivery whose Id is computed here
   {
-    const int64_t* base_tab = reinterpret_cast<const int64_t*>(hws + hlay.off_tables);
+    const int64_t* base_tab = reinterpret_cast<const int64_t*>(hws + hlay.off_tables) +
+                              (int64_t)hlay.stripe_level * (s.n + 1);
     const int64_t* tasks = reinterpret_cast<const int64_t*>(rws + rlay.off_tiles);
     const double* angles = reinterpret_cast<const double*>(rws + rlay.off_angles);
     // the task count is known on the device only; the tasks of every delivery
@@ -635,7 +646,7 @@ hipError_t launch_render_hash(const SetDesc& s, const HashLayout& hlay, const Re
       constexpr int RB = decltype(rbc)::value;
       auto launch = [&](auto kern) {
         hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, stream, s.table_dev, s.stride, s.n,
-                           plan_dev, tasks, angles, s.H, s.d, hsel, base_tab, nodes, o);
+                           plan_dev, tasks, angles, s.H, s.d, hsel, hlay.stripe_level, base_tab, nodes, o);
       };
       auto pick = [&](auto qpc) {
         constexpr bool QP = decltype(qpc)::value;
@@ -678,7 +689,8 @@ hipError_t launch_paged_render_hash(const PagedDesc& p, const HashLayout& hlay,
     return e;
   const uint8_t* hsel = rws + rlay.off_hsel;  // 0: slot delivery whose Id is computed here
   {
-    const int64_t* base_tab = reinterpret_cast<const int64_t*>(hws + hlay.off_tables);
+    const int64_t* base_tab = reinterpret_cast<const int64_t*>(hws + hlay.off_tables) +
+                              (int64_t)hlay.stripe_level * (s.n + 1);
     const int64_t* tasks = reinterpret_cast<const int64_t*>(rws + rlay.off_tiles);
     const double* angles = reinterpret_cast<const double*>(rws + rlay.off_angles);
     const int64_t cap = (int64_t)device_cu_count() * kFusedBlocksPerCu;
@@ -692,7 +704,7 @@ hipError_t launch_paged_render_hash(const PagedDesc& p, const HashLayout& hlay,
       auto launch = [&](auto kern) {
         hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, stream, pool, p.pages, p.b_shift,
                            s.table_dev, p.blocks_dev, k_table, v_table, s.n, plan_dev, tasks,
-                           angles, s.H, s.d, hsel, base_tab, nodes);
+                           angles, s.H, s.d, hsel, hlay.stripe_level, base_tab, nodes);
       };
       if (s.esize == 2) {
         if (style == CM_ROPE_HALF) launch(paged_hash_render_kernel<2, CM_ROPE_HALF, RB>);
