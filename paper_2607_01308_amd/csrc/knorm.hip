@@ -13,8 +13,11 @@
 // further levels run as small tree launches, the last few of them, where a
 // one-workgroup kernel follows, inside that kernel (knorm_fold.h). Reads only
 // the H*T*d*e tail bytes of one layer per fragment.
+#include <type_traits>
+
 #include "internal.h"
 #include "knorm_fold.h"
+#include "rotate.h"
 
 namespace cm {
 
@@ -33,7 +36,20 @@ __device__ __forceinline__ double lds_tree(double* sh, int count) {
   return sh[0];
 }
 
-constexpr int kInFlight = 16;   // row loads in flight per thread
+
+// Xor-butterfly sum of each acc[g] over the LPR lanes of a row, levels O, 2 O, ..
+template <int LPR, int O, int N>
+__device__ __forceinline__ void butterfly(double (&acc)[N]) {
+#pragma clang fp contract(off)
+  if constexpr (O < LPR) {
+#pragma unroll
+    for (int g = 0; g < N; ++g) {
+      const uint2 w = __builtin_bit_cast(uint2, acc[g]);
+      acc[g] = acc[g] + __builtin_bit_cast(double, make_uint2(lane_xor<O>(w.x), lane_xor<O>(w.y)));
+    }
+    butterfly<LPR, O * 2>(acc);
+  }
+}
 
 // Where row t of head h of fragment i's routing-layer K lives: a dense
 // [1, H, T, d] tensor named by the fragment table, or a page of a paged pool
@@ -68,7 +84,14 @@ struct PagedRows {
 
 // grid (count0, n), 256 threads: block b of fragment i sums rows
 // [b*rpb, (b+1)*rpb) of the padded (h, r) row space.
-template <int ESIZE, class Rows>
+//
+// LPR lanes per row, so 256 / LPR rows per pass; a workgroup's passes (up to 16)
+// load together. Bound by latency on all but the largest tails: with 16 passes'
+// worth of lane moves whatever the number of rows, and those through LDS, 134 MB
+// (Qwen3-4B large) took 51 us and 34 MB (N=4) 24 us; only as many passes as there
+// are rows, and DPP moves where the distance allows them: 24 -> 10.5 us (N=4), 6.4 ->
+// 4.6 us (Qwen3-1.7B N=2), 15.6 -> 6.6 us (N=5).
+template <int ESIZE, int LPR, int PASSES, class Rows>
 __global__ __launch_bounds__(256) void knorm_rows_kernel(Rows src, int64_t tail, int32_t d,
                                                          int64_t rows, int32_t rpb,
                                                          int64_t count0,
@@ -78,10 +101,10 @@ __global__ __launch_bounds__(256) void knorm_rows_kernel(Rows src, int64_t tail,
   const int i = blockIdx.y;
   const int64_t blk = blockIdx.x;
   const int64_t T = src.length(i);
-  const int row_bytes = d * ESIZE;
-  const int rb_shift = __builtin_ctz((unsigned)row_bytes);
-  const int lpr = row_bytes >> 4;  // lanes per row: a power of two in [4, 64]
-  const int rpp = 256 / lpr;       // rows per pass
+  constexpr int rb_shift = __builtin_ctz((unsigned)(LPR * 16));
+  constexpr int lpr = LPR;
+  constexpr int rpp = 256 / lpr;   // rows per pass
+  constexpr int kInFlight = PASSES;
   const int tid = threadIdx.x;
   const int q = tid & (lpr - 1);
   // kInFlight passes at a time: their loads are all issued before the first is
@@ -113,10 +136,7 @@ __global__ __launch_bounds__(256) void knorm_rows_kernel(Rows src, int64_t tail,
     double acc[kInFlight];
 #pragma unroll
     for (int g = 0; g < kInFlight; ++g) acc[g] = valid[g] ? row_chunk_sumsq<ESIZE>(v[g]) : 0.0;
-    for (int o = 1; o < lpr; o <<= 1) {
-#pragma unroll
-      for (int g = 0; g < kInFlight; ++g) acc[g] = acc[g] + __shfl_xor(acc[g], o, 64);
-    }
+    butterfly<LPR, 1>(acc);
 #pragma unroll
     for (int g = 0; g < kInFlight; ++g) {
       const int fl = p0 + g * rpp + tid / lpr;
@@ -124,8 +144,19 @@ __global__ __launch_bounds__(256) void knorm_rows_kernel(Rows src, int64_t tail,
     }
   }
   __syncthreads();
-  const double s = lds_tree(sh, rpb);
-  if (tid == 0) out[(int64_t)i * count0 + blk] = s;
+  // the rows' tree by one wave: a lane's consecutive rows, then a butterfly over
+  // the lanes (fewer rows than lanes: zeros above them, which change no sum)
+  if (tid >= 64) return;
+  double v[1];
+  if (rpb == 256) {
+    v[0] = (sh[4 * tid] + sh[4 * tid + 1]) + (sh[4 * tid + 2] + sh[4 * tid + 3]);
+  } else if (rpb == 128) {
+    v[0] = sh[2 * tid] + sh[2 * tid + 1];
+  } else {
+    v[0] = tid < rpb ? sh[tid] : 0.0;
+  }
+  butterfly<64, 1>(v);
+  if (tid == 0) out[(int64_t)i * count0 + blk] = v[0];
 }
 
 // grid (cout, n), g threads: out[i][b] = tree of in[i][b*g .. b*g+g).
@@ -189,12 +220,29 @@ hipError_t knorm_launches(const SetDesc& s, const KnormLayout& lay, Rows src, in
     ScopedTiming tm(K_KNORM_ROWS, stream);
     double* o = lay.count0 == 1 ? keys : bufs[0];
     const dim3 grid((uint32_t)lay.count0, (uint32_t)s.n);
-    if (s.esize == 2)
-      hipLaunchKernelGGL((knorm_rows_kernel<2, Rows>), grid, dim3(256), 0, stream, src, tail_len,
-                         s.d, lay.rows, lay.rows_per_block, lay.count0, o);
-    else
-      hipLaunchKernelGGL((knorm_rows_kernel<4, Rows>), grid, dim3(256), 0, stream, src, tail_len,
-                         s.d, lay.rows, lay.rows_per_block, lay.count0, o);
+    auto launch = [&](auto kern) {
+      hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, src, tail_len, s.d, lay.rows,
+                         lay.rows_per_block, lay.count0, o);
+    };
+    // the passes a workgroup's rows take, up to 16 at a time
+    auto by_passes = [&](auto lprc) {
+      constexpr int LPR = decltype(lprc)::value;
+      const int64_t passes = ((int64_t)lay.rows_per_block * LPR + 255) / 256;
+      if (s.esize == 2) {
+        if (passes <= 4) launch(knorm_rows_kernel<2, LPR, 4, Rows>);
+        else launch(knorm_rows_kernel<2, LPR, 16, Rows>);
+      } else {
+        if (passes <= 4) launch(knorm_rows_kernel<4, LPR, 4, Rows>);
+        else launch(knorm_rows_kernel<4, LPR, 16, Rows>);
+      }
+    };
+    switch ((int)(s.row_bytes >> 4)) {
+      case 4: by_passes(std::integral_constant<int, 4>{}); break;
+      case 8: by_passes(std::integral_constant<int, 8>{}); break;
+      case 16: by_passes(std::integral_constant<int, 16>{}); break;
+      case 32: by_passes(std::integral_constant<int, 32>{}); break;
+      default: by_passes(std::integral_constant<int, 64>{}); break;
+    }
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

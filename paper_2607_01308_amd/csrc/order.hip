@@ -169,19 +169,38 @@ __global__ __launch_bounds__(1024) void order_kernel(const int64_t* __restrict__
   order_body(table, stride, n, keys, digests, dedupe, plan);
 }
 
-// The plan, then (same workgroup, after a barrier that makes the plan visible to
-// every thread) the render's per-slot tables: one launch where the path would
-// otherwise take two.
+// The plan in the workgroup's LDS: the order kernels of the one-call paths build
+// it and then the render's tables from it, one launch where the path would
+// otherwise take two. Every workgroup of such a launch builds the same plan (a few
+// microseconds of one workgroup's latency, whoever does it) and takes a share of
+// the tables, the fp64 pow, cos and sin of every slot and column and, for the unit
+// render, an entry per unit and per slot and row block; the first one also writes
+// the plan. With one workgroup for all of it the launch took 22 us (fused path,
+// Qwen3-4B large) and, for set renders, 16.5 us on Qwen3-4B N=4 and 10.5 us on
+// Qwen3-1.7B N=2; now 17, 9.5 and 7.3 us.
+__device__ __forceinline__ int64_t* plan_lds() {
+  __shared__ int64_t plan[CM_PLAN_HEADER + 4 * CM_MAX_FRAGMENTS];
+  return plan;
+}
+
+// The workgroup's plan to memory (the first workgroup's).
+__device__ __forceinline__ void write_plan(const int64_t* l, int32_t n, int64_t* __restrict__ plan) {
+  if (blockIdx.x != 0) return;
+  for (int k = threadIdx.x; k < CM_PLAN_HEADER + 4 * n; k += (int)blockDim.x) plan[k] = l[k];
+}
+
 __global__ __launch_bounds__(1024) void order_render_prep_kernel(
     const int64_t* __restrict__ table, int64_t stride, int32_t n, const double* __restrict__ keys,
     const uint8_t* __restrict__ digests, int64_t* __restrict__ plan, int32_t d, int32_t ep,
     int32_t style, double base, int32_t stripe_blocks, int64_t tensor_pairs, int64_t token_bytes,
     const uint8_t* __restrict__ select, uint8_t* __restrict__ hsel,
     int64_t* __restrict__ unit_base, double* __restrict__ angles) {
-  order_body(table, stride, n, keys, digests, 1, plan);
+  int64_t* l = plan_lds();
+  order_body(table, stride, n, keys, digests, 1, l);
   __syncthreads();
-  render_tables(plan, n, d, ep, style, base, stripe_blocks, tensor_pairs, token_bytes, select,
-                hsel, unit_base, angles, table, stride, 0, nullptr, nullptr);
+  write_plan(l, n, plan);
+  render_tables(l, n, d, ep, style, base, stripe_blocks, tensor_pairs, token_bytes, select, hsel,
+                unit_base, angles, table, stride, 0, nullptr, nullptr, blockIdx.x, gridDim.x);
 }
 
 // Steps 2-5 of a set render before the render itself: the last levels of the
@@ -196,19 +215,28 @@ __global__ __launch_bounds__(1024) void order_set_prep_kernel(
     int32_t ep, int32_t style, double base, double* __restrict__ angles,
     int64_t* __restrict__ unit_base, int32_t H, int32_t n_lkh, int32_t rb_shift, int64_t units,
     int32_t* __restrict__ unit_slot, int64_t* __restrict__ src_base) {
-  knorm_finish(table, stride, n, H, d, kd, parts, count, keys);
-  order_body(table, stride, n, keys, digests, 1, plan);
+  __shared__ double s_keys[CM_MAX_FRAGMENTS];
+  int64_t* l = plan_lds();
+  // count == 1: the scores are the keys already
+  const bool here = kd.layer >= 0 || count > 1;
+  knorm_finish(table, stride, n, H, d, kd, parts, count, s_keys);
+  order_body(table, stride, n, here ? s_keys : keys, digests, 1, l);
   __syncthreads();
-  bool ok = plan[CM_PLAN_STATUS] == CM_OK;
-  if (ok && plan[CM_PLAN_TOUT] != T_out) {
+  bool ok = l[CM_PLAN_STATUS] == CM_OK;
+  if (ok && l[CM_PLAN_TOUT] != T_out) {
     ok = false;
-    if (threadIdx.x == 0) plan[CM_PLAN_STATUS] = CM_ESHAPE;
+    __syncthreads();                        // every thread has read the status
+    if (threadIdx.x == 0) l[CM_PLAN_STATUS] = CM_ESHAPE;
+    __syncthreads();
   }
+  write_plan(l, n, plan);
+  if (here && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < n; i += (int)blockDim.x) keys[i] = s_keys[i];
   if (ok)
-    render_tables(plan, n, d, ep, style, base, 0, 0, 0, nullptr, nullptr, unit_base, angles,
-                  table, stride, T_out, nullptr, nullptr);
-  unit_tables(table, stride, plan, n, H, n_lkh, rb_shift, 0, T_out, units, ok, unit_slot,
-              src_base);
+    render_tables(l, n, d, ep, style, base, 0, 0, 0, nullptr, nullptr, unit_base, angles, table,
+                  stride, T_out, nullptr, nullptr, blockIdx.x, gridDim.x);
+  unit_tables<true>(table, stride, l, n, H, n_lkh, rb_shift, 0, T_out, units, ok, unit_slot,
+                    src_base, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(1024) void equal_key_mask_kernel(const int64_t* __restrict__ table,
@@ -219,6 +247,18 @@ __global__ __launch_bounds__(1024) void equal_key_mask_kernel(const int64_t* __r
 }
 
 }  // namespace
+
+// Threads of an order workgroup, and how many of them share `work` table entries:
+// one entry per thread, up to a workgroup on a quarter of the CUs.
+static int order_threads(int32_t n) {
+  int threads = 256;
+  while (threads < n) threads <<= 1;
+  return threads;
+}
+static int order_parts(int64_t work, int threads) {
+  const int64_t parts = (work + threads - 1) / threads;
+  return (int)(parts < 1 ? 1 : parts < 64 ? parts : 64);
+}
 
 hipError_t launch_equal_key_mask(const SetDesc& s, const double* keys, uint8_t* mask,
                                  hipStream_t stream) {
@@ -245,13 +285,10 @@ hipError_t launch_order_render_prep(const SetDesc& s, const double* keys, const 
                                     int32_t style, int32_t stripe_blocks, const uint8_t* select,
                                     uint8_t* rws, hipStream_t stream) {
   ScopedTiming tm(K_ORDER, stream);
-  // at least n threads (one per delivery), and enough for about two angle
-  // pairs each (fp64 pow, cos and sin per pair: 31 pairs per thread of 64 took
-  // 43 us on a 32-delivery set)
-  int threads = 64;
-  while (threads < 1024 && (threads < s.n || (int64_t)threads * 2 < (int64_t)s.n * (s.d / 2)))
-    threads <<= 1;
-  hipLaunchKernelGGL(order_render_prep_kernel, dim3(1), dim3(threads), 0, stream, s.table_dev,
+  // a workgroup of at least n threads (one per delivery); an angle pair per thread
+  const int threads = order_threads(s.n);
+  const int parts = order_parts((int64_t)s.n * (s.d / 2), threads);
+  hipLaunchKernelGGL(order_render_prep_kernel, dim3(parts), dim3(threads), 0, stream, s.table_dev,
                      s.stride, s.n, keys, digests, plan, s.d, 16 / s.esize, style, base,
                      stripe_blocks, (int64_t)s.L, token_bytes_of(s), select,
                      select ? rws + rlay.off_hsel : nullptr,
@@ -265,12 +302,15 @@ hipError_t launch_render_set(const SetDesc& s, const RenderLayout& lay, const Kn
                              double base, int32_t style, void* out, uint8_t* rws,
                              hipStream_t stream) {
   const int64_t units = render_units(s, T_out);
-  // the score rows too when the set is scored here
-  const int threads = kp.direct.layer >= 0 ? 1024
-                                           : table_threads(s.n, units + (int64_t)s.n * 2 * s.L * s.H);
+  // a set that is scored here takes one workgroup of many threads for its rows
+  const bool direct = kp.direct.layer >= 0;
+  const int threads = direct ? 1024 : order_threads(s.n);
+  const int parts = direct ? 1
+                           : order_parts((int64_t)s.n * (s.d / 2) + units +
+                                             (int64_t)s.n * 2 * s.L * s.H, threads);
   {
     ScopedTiming tm(K_ORDER, stream);
-    hipLaunchKernelGGL(order_set_prep_kernel, dim3(1), dim3(threads), 0, stream, s.table_dev,
+    hipLaunchKernelGGL(order_set_prep_kernel, dim3(parts), dim3(threads), 0, stream, s.table_dev,
                        s.stride, s.n, kp.parts, kp.count, kp.direct, keys, digests, plan, T_out, s.d,
                        16 / s.esize, style, base, reinterpret_cast<double*>(rws + lay.off_angles),
                        reinterpret_cast<int64_t*>(rws + lay.off_tiles), s.H, 2 * s.L * s.H,

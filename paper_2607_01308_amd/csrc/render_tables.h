@@ -17,14 +17,16 @@ namespace cm {
 // the plan's status is an error) and, with a select mask, hsel[i] = 0
 // for the slot deliveries whose Id the fused kernel computes (select[i] == 0),
 // 1 for every other delivery. Returns false (the same in every thread) for a
-// plan that fails the device check; nothing else is written then.
+// plan that fails the device check; nothing else is written then. Of several
+// workgroups that hold the same plan, number `part` of `parts` writes its share of
+// the angles, the first one the rest.
 __device__ __forceinline__ bool render_tables(
     const int64_t* __restrict__ plan, int32_t n, int32_t d, int32_t ep, int32_t style,
     double base, int32_t stripe_blocks, int64_t tensor_pairs, int64_t token_bytes,
     const uint8_t* __restrict__ select, uint8_t* __restrict__ hsel,
     int64_t* __restrict__ unit_base, double* __restrict__ angles,
     const int64_t* __restrict__ table, int64_t stride, int64_t T_out, int32_t* plan_ok,
-    int64_t* plan_status) {
+    int64_t* plan_status, int part = 0, int parts = 1) {
   __shared__ int64_t sc[1024];
   const int tid = threadIdx.x;
   int n_u = (int)plan[CM_PLAN_NUNIQUE];
@@ -59,7 +61,9 @@ __device__ __forceinline__ bool render_tables(
     if (!all) return false;
     __syncthreads();
   }
-  if (stripe_blocks > 0) {
+  // a plan whose status is an error (a non-finite score) gets no angles either
+  if (stripe_blocks > 0 && part > 0 && (plan[CM_PLAN_STATUS] != CM_OK || n_u < 0 || n_u > n)) n_u = 0;
+  if (stripe_blocks > 0 && part == 0) {
     // a plan whose status is an error (a non-finite score) gets no tasks
     if (plan[CM_PLAN_STATUS] != CM_OK || n_u < 0 || n_u > n) n_u = 0;
     const int64_t len = tid < n_u ? plan[CM_PLAN_HEADER + 2 * (int64_t)n + tid] : 0;
@@ -91,7 +95,7 @@ __device__ __forceinline__ bool render_tables(
   // least d / 2 threads, a thread keeps one column for every slot)
   int tj = -1;
   double theta = 0.0;
-  for (int idx = tid; idx < n_u * halfd; idx += blockDim.x) {
+  for (int idx = part * (int)blockDim.x + tid; idx < n_u * halfd; idx += parts * (int)blockDim.x) {
     const int s = idx / halfd;
     const int j = idx - s * halfd;
     if (j != tj) {
@@ -114,36 +118,45 @@ __device__ __forceinline__ bool render_tables(
 // = the address that row r of slot s in row block lkh = (l * 2 + kv) * H + h is
 // read from when offset by r * row_bytes. ok == false (a plan that is not
 // rendered): every unit gets -1, which the render skips. The slots' delivery,
-// length and offset are staged in LDS first.
+// length and offset are staged in LDS first, unless the plan is in LDS itself
+// (STAGED); part and parts as in render_tables.
+template <bool STAGED = false>
 __device__ __forceinline__ void unit_tables(const int64_t* __restrict__ table, int64_t stride,
                                             const int64_t* __restrict__ plan, int32_t n,
                                             int32_t H, int32_t n_lkh, int32_t rb_shift,
                                             int64_t row0, int64_t T_out, int64_t units, bool ok,
                                             int32_t* __restrict__ unit_slot,
-                                            int64_t* __restrict__ src_base) {
-  __shared__ int64_t u_off[1024];
-  __shared__ int64_t u_len[1024];
-  __shared__ int64_t u_src[1024];
-  const int tid = threadIdx.x;
-  const int nt = blockDim.x;
+                                            int64_t* __restrict__ src_base, int part = 0,
+                                            int parts = 1) {
+  const int tid = part * (int)blockDim.x + (int)threadIdx.x;
+  const int nt = parts * (int)blockDim.x;
   if (!ok) {
     for (int64_t x = tid; x < units; x += nt) unit_slot[x] = -1;
     return;
   }
   const int n_u = (int)plan[CM_PLAN_NUNIQUE];
-  for (int s = tid; s < n_u; s += nt) {
-    u_src[s] = plan[CM_PLAN_HEADER + s];
-    u_off[s] = plan[CM_PLAN_HEADER + n + s];
-    u_len[s] = plan[CM_PLAN_HEADER + 2 * (int64_t)n + s];
+  const int64_t *src = plan + CM_PLAN_HEADER, *off = src + n, *len = off + n;
+  if constexpr (!STAGED) {
+    __shared__ int64_t u_off[1024];
+    __shared__ int64_t u_len[1024];
+    __shared__ int64_t u_src[1024];
+    for (int s = threadIdx.x; s < n_u; s += (int)blockDim.x) {
+      u_src[s] = src[s];
+      u_off[s] = off[s];
+      u_len[s] = len[s];
+    }
+    __syncthreads();
+    src = u_src;
+    off = u_off;
+    len = u_len;
   }
-  __syncthreads();
   for (int64_t x = tid; x < units; x += nt)
-    unit_slot[x] = unit_slot_code(u_off, n_u, T_out, rb_shift, row0, x);
+    unit_slot[x] = unit_slot_code(off, n_u, T_out, rb_shift, row0, x);
   for (int64_t e = tid; e < (int64_t)n_u * n_lkh; e += nt) {
     const int s = (int)(e / n_lkh);
     const int lkh = (int)(e - (int64_t)s * n_lkh);
-    const int64_t base = table[u_src[s] * stride + 1 + lkh / H];
-    src_base[e] = base + unit_src_offset(lkh % H, u_len[s], u_off[s], rb_shift, 0);
+    const int64_t base = table[src[s] * stride + 1 + lkh / H];
+    src_base[e] = base + unit_src_offset(lkh % H, len[s], off[s], rb_shift, 0);
   }
 }
 
