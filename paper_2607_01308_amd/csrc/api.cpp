@@ -1029,18 +1029,29 @@ int32_t cm_paged_deliveries(const cm_pagedset* set, int32_t routing_layer, int64
   const int64_t nbo_cap = (T_all + p.block - 1) / p.block;
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   hipStream_t sm = static_cast<hipStream_t>(stream);
-  // steps 1-3 (the colliding deliveries' Ids), the block tables, then the
-  // render with every other Id from its loads, in workspace that each step
-  // takes over from the one before
-  hipError_t e = enqueue_paged_order(p, routing_layer, tail_len, keys_dev, mask_dev, digests_dev,
-                                     plan_dev, ws, sm);
+  // the dense path's launches over paged addressing (cm_render_deliveries), with
+  // the block tables between the order and the render
+  const cm::SetDesc& s = p.s;
+  cm::KnormPartials kp{};
+  hipError_t e = cm::launch_knorm_paged_partial(p, cm::knorm_layout(s, tail_len), routing_layer,
+                                                tail_len, keys_dev, ws, sm, cm::kKnormFoldMax, &kp);
+  const cm::HashLayout hlay = cm::hash_layout(s);
+  const cm::RenderLayout rlay = cm::render_layout(s);
+  if (e == hipSuccess) e = cm::launch_mask_hash_prep(s, hlay, kp, keys_dev, mask_dev, ws, sm);
+  if (e == hipSuccess)
+    e = cm::launch_hash_paged(p, hlay, mask_dev, 1, digests_dev, ws, sm, 0, true);
+  uint8_t* rws = ws + cm::align_up(hlay.bytes, cm::kWsAlign);
+  if (e == hipSuccess)
+    e = cm::launch_order_render_prep(s, keys_dev, digests_dev, plan_dev, rlay, rope->base,
+                                     rope->style, (int32_t)cm::kStripeBlocks, mask_dev, rws, sm);
   if (e == hipSuccess)
     e = cm::launch_paged_tables(p, plan_dev, free_dev, n_free, nbo_cap, k_table_dev, v_table_dev,
-                                n_fresh_dev, sm);
+                                n_fresh_dev,
+                                reinterpret_cast<int64_t*>(rws + rlay.off_tiles) + s.n,
+                                rws + rlay.off_hsel, sm);
   if (e == hipSuccess)
-    e = cm::launch_paged_render_hash(p, cm::hash_layout(p.s), cm::render_layout(p.s), plan_dev,
-                                     rope->base, rope->style, mask_dev, k_table_dev, v_table_dev,
-                                     digests_dev, ws, sm);
+    e = cm::launch_paged_render_hash(p, hlay, rlay, plan_dev, rope->base, rope->style, mask_dev,
+                                     k_table_dev, v_table_dev, digests_dev, ws, sm, true);
   return e == hipSuccess ? CM_OK : fail_hip(e, "cm_paged_deliveries");
 }
 

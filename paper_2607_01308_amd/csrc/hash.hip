@@ -621,10 +621,10 @@ hipError_t launch_hash(const SetDesc& s, const HashLayout& lay, const uint8_t* s
 
 hipError_t launch_hash_paged(const PagedDesc& p, const HashLayout& lay, const uint8_t* select,
                              uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
-                             int blocks_per_cu) {
+                             int blocks_per_cu, bool tables_ready) {
   const SetDesc& s = p.s;
-  hipError_t e = launch_hash_prep(s, lay, ws, stream);
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
+  if (!tables_ready && (e = launch_hash_prep(s, lay, ws, stream)) != hipSuccess) return e;
   {
     int64_t* base = reinterpret_cast<int64_t*>(ws + lay.off_tables);
     const int64_t nb1 = s.n + 1;

@@ -221,28 +221,34 @@ struct PagedDesc {
 // Steps 1-2 on paged fragments: scores (full tree) and the Id of every fragment
 // (the same content address as the dense form's: each tensor hashed in the
 // byte order of its dense layout).
+hipError_t launch_knorm_paged_partial(const PagedDesc& p, const KnormLayout& lay, int32_t layer,
+                                      int64_t tail_len, double* keys, uint8_t* ws,
+                                      hipStream_t stream, int64_t fold_max, KnormPartials* out);
 hipError_t launch_knorm_paged(const PagedDesc& p, const KnormLayout& lay, int32_t layer,
                               int64_t tail_len, double* keys, uint8_t* ws, hipStream_t stream);
 // select as launch_hash; blocks_per_cu > 0 caps the chunk kernel's persistent
 // grid (fewer workgroups leave room for a kernel running beside it).
 hipError_t launch_hash_paged(const PagedDesc& p, const HashLayout& lay, const uint8_t* select,
                              uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
-                             int blocks_per_cu = 0);
+                             int blocks_per_cu = 0, bool tables_ready = false);
 // Steps 1 and 4-5 in one pass over paged storage: the render of the fragment
 // rows into the pages of the merged K and V block tables (rows whose merged
 // page is the page they are read from are left in place) and, for the slot
 // deliveries with select[i] == 0, their Ids (hsel as launch_render_hash).
 // Workspace: the hash layout, then the render layout (launch_render_hash's).
+// prep_ready: it holds the node tables and the render's per-slot tables already.
 hipError_t launch_paged_render_hash(const PagedDesc& p, const HashLayout& hlay,
                                     const RenderLayout& rlay, const int64_t* plan_dev, double base,
                                     int32_t style, const uint8_t* select, const int32_t* k_table,
                                     const int32_t* v_table, uint8_t* digests, uint8_t* ws,
-                                    hipStream_t stream);
+                                    hipStream_t stream, bool prep_ready = false);
 // Merged K and V block tables of the plan on the device (cm_paged_tables' rule;
-// paged.hip). nbo_cap: the tables' capacity in blocks.
+// paged.hip). nbo_cap: the tables' capacity in blocks; task_total, hsel: the
+// fused render's task count and Id mask, cleared if the plan is refused.
 hipError_t launch_paged_tables(const PagedDesc& p, int64_t* plan_dev, const int32_t* free_dev,
                                int64_t n_free, int64_t nbo_cap, int32_t* k_table,
-                               int32_t* v_table, int64_t* n_fresh, hipStream_t stream);
+                               int32_t* v_table, int64_t* n_fresh, int64_t* task_total,
+                               uint8_t* hsel, hipStream_t stream);
 hipError_t launch_paged_render(const PagedDesc& p, const int64_t* plan_dev, int32_t n_unique,
                                double base, int32_t style, const int32_t* k_table,
                                const int32_t* v_table, const int32_t* fresh, int64_t n_fresh,

@@ -284,12 +284,18 @@ hipError_t launch_knorm_partial(const SetDesc& s, const KnormLayout& lay, int32_
                         stream, fold_max, out);
 }
 
+hipError_t launch_knorm_paged_partial(const PagedDesc& p, const KnormLayout& lay, int32_t layer,
+                                      int64_t tail_len, double* keys, uint8_t* ws,
+                                      hipStream_t stream, int64_t fold_max, KnormPartials* out) {
+  const PagedRows src{static_cast<const uint8_t*>(p.pool), p.s.table_dev, p.blocks_dev, p.pages,
+                      p.s.H, p.b_shift, layer};
+  return knorm_launches(p.s, lay, src, tail_len, keys, ws, stream, fold_max, out);
+}
+
 hipError_t launch_knorm_paged(const PagedDesc& p, const KnormLayout& lay, int32_t layer,
                               int64_t tail_len, double* keys, uint8_t* ws, hipStream_t stream) {
   KnormPartials kp;
-  const PagedRows src{static_cast<const uint8_t*>(p.pool), p.s.table_dev, p.blocks_dev, p.pages,
-                      p.s.H, p.b_shift, layer};
-  return knorm_launches(p.s, lay, src, tail_len, keys, ws, stream, 1, &kp);
+  return launch_knorm_paged_partial(p, lay, layer, tail_len, keys, ws, stream, 1, &kp);
 }
 
 hipError_t launch_knorm(const SetDesc& s, const KnormLayout& lay, int32_t layer, int64_t tail_len,

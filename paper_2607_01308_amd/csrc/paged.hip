@@ -167,18 +167,28 @@ __global__ __launch_bounds__(64) void paged_render_kernel(
 // `free` in block order, K before V. Each thread takes a run of consecutive
 // blocks: a count, a scan of the counts, then the assignment. A free list too
 // short for the plan leaves the tables unwritten and the plan's status
-// CM_EINVAL (n_fresh: the pages needed), so nothing is rendered; a plan whose
-// status is already an error is left as it is (n_fresh: 0).
+// CM_EINVAL (n_fresh: the pages needed), and takes the fused render's tasks and
+// Ids back (task_total, hsel: built for the plan before), so nothing is rendered; a
+// plan whose status is already an error is left as it is (n_fresh: 0).
 __global__ __launch_bounds__(1024) void paged_tables_kernel(
     int64_t* __restrict__ plan, int32_t n, const int64_t* __restrict__ table,
     const int32_t* __restrict__ blocks, int32_t b_shift, const int32_t* __restrict__ free_pages,
     int64_t n_free, int64_t nbo_cap, int32_t* __restrict__ k_table,
-    int32_t* __restrict__ v_table, int64_t* __restrict__ n_fresh) {
+    int32_t* __restrict__ v_table, int64_t* __restrict__ n_fresh,
+    int64_t* __restrict__ task_total, uint8_t* __restrict__ hsel) {
   __shared__ int64_t s_off[CM_MAX_FRAGMENTS];
   __shared__ int64_t s_len[CM_MAX_FRAGMENTS];
   __shared__ int64_t s_first[CM_MAX_FRAGMENTS];
   __shared__ int64_t scan[1024];
   const int tid = threadIdx.x, nt = blockDim.x;
+  auto refuse = [&](int64_t pages, int64_t status) {
+    for (int i = tid; i < n; i += nt) hsel[i] = 1;
+    if (tid == 0) {
+      *n_fresh = pages;
+      *task_total = 0;
+      plan[CM_PLAN_STATUS] = status;
+    }
+  };
   if (plan[CM_PLAN_STATUS] != CM_OK) {
     if (tid == 0) *n_fresh = 0;
     return;
@@ -188,10 +198,7 @@ __global__ __launch_bounds__(1024) void paged_tables_kernel(
   const int64_t B = (int64_t)1 << b_shift;
   const int64_t nbo = (T_out + B - 1) >> b_shift;
   if (n_u < 1 || n_u > n || nbo > nbo_cap) {     // not a plan of this set (checked on the
-    if (tid == 0) {                              // host for every other entry point)
-      *n_fresh = 0;
-      plan[CM_PLAN_STATUS] = CM_ESHAPE;
-    }
+    refuse(0, CM_ESHAPE);                        // host for every other entry point)
     return;
   }
   for (int s = tid; s < n_u; s += nt) {
@@ -242,10 +249,7 @@ __global__ __launch_bounds__(1024) void paged_tables_kernel(
   }
   const int64_t total = scan[nt - 1];
   if (total > n_free) {
-    if (tid == 0) {
-      *n_fresh = total;
-      plan[CM_PLAN_STATUS] = CM_EINVAL;
-    }
+    refuse(total, CM_EINVAL);
     return;
   }
   int64_t next = scan[tid] - cnt;
@@ -264,11 +268,12 @@ __global__ __launch_bounds__(1024) void paged_tables_kernel(
 
 hipError_t launch_paged_tables(const PagedDesc& p, int64_t* plan_dev, const int32_t* free_dev,
                                int64_t n_free, int64_t nbo_cap, int32_t* k_table,
-                               int32_t* v_table, int64_t* n_fresh, hipStream_t stream) {
+                               int32_t* v_table, int64_t* n_fresh, int64_t* task_total,
+                               uint8_t* hsel, hipStream_t stream) {
   ScopedTiming tm(K_RENDER_PREP, stream);
   hipLaunchKernelGGL(paged_tables_kernel, dim3(1), dim3(1024), 0, stream, plan_dev, p.s.n,
                      p.s.table_dev, p.blocks_dev, p.b_shift, free_dev, n_free, nbo_cap, k_table,
-                     v_table, n_fresh);
+                     v_table, n_fresh, task_total, hsel);
   return hipGetLastError();
 }
 

@@ -678,14 +678,15 @@ hipError_t launch_paged_render_hash(const PagedDesc& p, const HashLayout& hlay,
                                     const RenderLayout& rlay, const int64_t* plan_dev, double base,
                                     int32_t style, const uint8_t* select, const int32_t* k_table,
                                     const int32_t* v_table, uint8_t* digests, uint8_t* ws,
-                                    hipStream_t stream) {
+                                    hipStream_t stream, bool prep_ready) {
   const SetDesc& s = p.s;
   uint8_t* hws = ws;
   uint8_t* rws = ws + align_up(hlay.bytes, kWsAlign);
-  hipError_t e = launch_hash_prep(s, hlay, hws, stream);
-  if (e != hipSuccess) return e;
-  if ((e = launch_render_prep(s, rlay, plan_dev, s.n, base, style, (int32_t)kStripeBlocks, select,
-                              rws, stream)) != hipSuccess)
+  hipError_t e = hipSuccess;
+  if (!prep_ready && (e = launch_hash_prep(s, hlay, hws, stream)) != hipSuccess) return e;
+  if (!prep_ready && (e = launch_render_prep(s, rlay, plan_dev, s.n, base, style,
+                                             (int32_t)kStripeBlocks, select, rws, stream)) !=
+                         hipSuccess)
     return e;
   const uint8_t* hsel = rws + rlay.off_hsel;  // 0: slot delivery whose Id is computed here
   {
