@@ -49,19 +49,22 @@ class FragmentBatch:
         self.device = torch.device(device) if device is not None else first_k.device
         if self.device.type != "cuda":
             raise ValueError("fragments must live on a GPU")
+        dtype, device = self.torch_dtype, self.device
         rows = []
         for i, cache in enumerate(caches):
             if len(cache) != self.L:
                 raise ValueError(f"fragment {i} has {len(cache)} layers, expected {self.L}")
             T = cache[0][0].shape[2]
             row = [T]
+            want = (1, self.H, T, self.d)
             for l, (K, V) in enumerate(cache):
                 for x in (K, V):
-                    if (x.dim() != 4 or x.shape[0] != 1 or x.shape[1] != self.H or x.shape[2] != T
-                            or x.shape[3] != self.d):
+                    # (one comparison of the whole shape: a deep model's batch holds
+                    # hundreds of tensors, and a batch is described for every arrival)
+                    if x.shape != want:
                         raise ValueError(f"fragment {i} layer {l}: shape {tuple(x.shape)} is not "
                                          f"[1, {self.H}, {T}, {self.d}]")
-                    if x.dtype != self.torch_dtype or x.device != self.device:
+                    if x.dtype is not dtype or x.device != device:
                         raise ValueError(f"fragment {i} layer {l}: dtype/device differ from the set")
                     if not x.is_contiguous():
                         raise ValueError(f"fragment {i} layer {l}: tensor is not contiguous")
