@@ -628,22 +628,29 @@ int32_t render_deliveries_common(const cm_fragset* set, int32_t routing_layer, i
   hipError_t e = cm::launch_knorm_partial(s, cm::knorm_layout(s, tail_len), routing_layer,
                                           tail_len, keys_dev, ws, sm, cm::kKnormFoldMax, &kp);
   const cm::HashLayout hlay = cm::hash_layout(s);
+  const cm::RenderLayout rlay = cm::render_layout(s);
+  // re-deliveries by their bytes, from 256 MiB of deliveries on: comparing them
+  // takes a launch (about 4 us when no scores are equal), hashing 256 MiB 70 us
+  uint8_t* rws = ws + cm::align_up(hlay.bytes, cm::kWsAlign);
+  int32_t* lead = reinterpret_cast<int32_t*>(rws + rlay.off_src_base);
+  const cm::CopyTables tables{keys_dev, lead, lead + s.n};
+  const cm::CopyTables* ct = s.n > 1 && hlay.tasks >= 4096 ? &tables : nullptr;
   // the last score levels, the key mask and the hash trees' node tables in one
   // launch (the tables depend only on the lengths); it reads the score partials
   // before it writes over them
-  if (e == hipSuccess) e = cm::launch_mask_hash_prep(s, hlay, kp, keys_dev, mask_dev, ws, sm);
-  if (e == hipSuccess) e = cm::launch_hash(s, hlay, mask_dev, 1, digests_dev, ws, sm, true);
+  if (e == hipSuccess) e = cm::launch_mask_hash_prep(s, hlay, kp, keys_dev, mask_dev, ws, sm, ct);
+  if (e == hipSuccess && ct) e = cm::launch_copies(s, hlay, *ct, sm);
+  if (e == hipSuccess) e = cm::launch_hash(s, hlay, mask_dev, 1, digests_dev, ws, sm, true, ct);
   // the order kernel also builds the render's per-slot tables; the node-base
   // tables written for the first Ids are still in the workspace (the render's
   // tables live after them), so the fused pass reuses both
-  const cm::RenderLayout rlay = cm::render_layout(s);
   if (e == hipSuccess)
     e = cm::launch_order_render_prep(s, keys_dev, digests_dev, plan_dev, rlay, rope->base,
-                                     rope->style, (int32_t)cm::kStripeBlocks, mask_dev,
-                                     ws + cm::align_up(hlay.bytes, cm::kWsAlign), sm);
+                                     rope->style, (int32_t)cm::kStripeBlocks, mask_dev, rws,
+                                     sm, ct);
   if (e == hipSuccess)
     e = cm::launch_render_hash(s, hlay, rlay, plan_dev, rope->base, rope->style, mask_dev,
-                               digests_dev, out_dev, ws, sm, true, true);
+                               digests_dev, out_dev, ws, sm, true, true, ct);
   return e == hipSuccess ? CM_OK : fail_hip(e, where);
 }
 

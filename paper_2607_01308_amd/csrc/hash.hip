@@ -112,11 +112,77 @@ __global__ __launch_bounds__(1024) void hash_prep_kernel(const int64_t* __restri
 __global__ __launch_bounds__(1024) void mask_hash_prep_kernel(
     const int64_t* __restrict__ table, int32_t n, int64_t stride, int64_t token_bytes, int32_t L,
     int32_t levels, const double* parts, int64_t count, KnormDirect kd, int32_t H, int32_t d,
-    double* keys, uint8_t* __restrict__ mask, int64_t* base, int32_t* __restrict__ arrived) {
+    double* keys, uint8_t* __restrict__ mask, int64_t* base, int32_t* __restrict__ arrived,
+    int32_t* lead, int32_t* differs) {
   knorm_finish(table, stride, n, H, d, kd, parts, count, keys);
-  equal_key_mask_body(n, keys, mask);
+  equal_key_mask_body(n, keys, mask, table, stride, lead, differs);
   hash_tables(table, n, stride, token_bytes, L, levels, base, arrived);
 }
+
+// differs[i] = 1 for every delivery i whose bytes are not those of lead[i] (the
+// same length). Bound by HBM: both are read once, where hashing them costs the
+// VALU more than that and the copies would be hashed to no other use (1.16 GB of
+// deliveries with equal keys, six of ten of them copies: hashing them and their
+// trees took 340 us, and the whole path 721; with this it takes 628). A wave
+// takes 64 KiB at a time, 8 KiB of each side in flight, and leaves a delivery
+// that is known to differ.
+__global__ __launch_bounds__(kBlock) void copy_kernel(const int64_t* __restrict__ table, int32_t n,
+                                                      int64_t stride, int64_t token_bytes,
+                                                      int32_t L, const int32_t* __restrict__ lead,
+                                                      int32_t* differs) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wave
+  const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
+  const int64_t first = (int64_t)blockIdx.x * (kBlock / 64) + wave;
+  for (int i = 0; i < n; ++i) {
+    const int l = lead[i];
+    if (l == i) continue;
+    const int64_t bytes = table[(int64_t)i * stride] * token_bytes;
+    const int64_t stripes = stripes_of(bytes);
+    for (int64_t task = first; task < 2 * L * stripes; task += waves) {
+      if (__hip_atomic_load(&differs[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
+      const int64_t t = task / stripes;
+      const int64_t b0 = (task - t * stripes) << 16;
+      const int64_t len = bytes - b0 < 65536 ? bytes - b0 : 65536;
+      const uint8_t* a = reinterpret_cast<const uint8_t*>(table[(int64_t)i * stride + 1 + t]) + b0;
+      const uint8_t* b = reinterpret_cast<const uint8_t*>(table[(int64_t)l * stride + 1 + t]) + b0;
+      bool other = false;
+      for (int64_t o = 0; o < len && !other; o += 8192) {
+        u32x4 x[8], y[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int64_t c = o + 1024 * k + lane * 16;
+          x[k] = y[k] = u32x4{0u, 0u, 0u, 0u};
+          if (c < len) {
+            x[k] = *global_ptr<u32x4>(a + c);
+            y[k] = *global_ptr<u32x4>(b + c);
+          }
+        }
+        uint32_t d = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          d |= (x[k][0] ^ y[k][0]) | (x[k][1] ^ y[k][1]) | (x[k][2] ^ y[k][2]) | (x[k][3] ^ y[k][3]);
+        other = __builtin_amdgcn_ballot_w64(d != 0) != 0;
+      }
+      if (other && lane == 0)
+        __hip_atomic_store(&differs[i], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
+// Whether the Id of delivery i (the same on every lane) is computed in this pass:
+// those with select[i] == want, of them before the order only the needed ones
+// (key_mask.h).
+struct HashPass {
+  const uint8_t* select;
+  uint32_t want;
+  bool early;        // the pass before the order, with copies known
+  Copies copies;
+  __device__ __forceinline__ bool takes(int i, int32_t n, int lane) const {
+    if (select && select[i] != want) return false;
+    return !early || copies.needed(i, n, lane);
+  }
+};
 
 // One wave = one (tensor, stripe) task at a time: lane k hashes chunk k of the
 // stripe, 1 KiB of consecutive bytes (the tensor's last chunk may be shorter,
@@ -128,9 +194,7 @@ __global__ __launch_bounds__(kBlock) void hash_chunk_kernel(const int64_t* __res
                                                             int32_t level,
                                                             const int64_t* __restrict__ base_v,
                                                             const int64_t* __restrict__ task_base,
-                                                            int64_t total_tasks,
-                                                            const uint8_t* __restrict__ select,
-                                                            uint32_t want,
+                                                            int64_t total_tasks, HashPass pass,
                                                             uint8_t* __restrict__ nodes) {
   __shared__ __attribute__((aligned(16))) uint32_t fold_lds[kBlock / 64][kStripeChunks * 8];
   const int lane = threadIdx.x & 63;
@@ -139,7 +203,7 @@ __global__ __launch_bounds__(kBlock) void hash_chunk_kernel(const int64_t* __res
   for (int64_t task = (int64_t)blockIdx.x * (kBlock / 64) + wave; task < total_tasks;
        task += waves) {
     const int i = find_fragment(task_base, n, task);
-    if (select && select[i] != want) continue;
+    if (!pass.takes(i, n, lane)) continue;
     const int64_t bytes = table[(int64_t)i * stride] * token_bytes;
     const int64_t stripes = stripes_of(bytes);
     const int64_t m = chunks_of(bytes);
@@ -399,6 +463,26 @@ __device__ __forceinline__ void fragment_id(uint64_t T, const IdShape& sh,
   if (lane < 8) reinterpret_cast<uint32_t*>(digest)[lane] = group_cv[lane];
 }
 
+// The Id just computed by this wave for delivery i to i's copies.
+__device__ __forceinline__ void copy_digest(const Copies& copies, int i, int32_t n,
+                                            uint8_t* digests, int lane) {
+  if (!copies.lead) return;
+  // fragment_id's last step left the words in lanes 0 .. 7 of this wave's stores
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  const uint32_t* id = reinterpret_cast<const uint32_t*>(digests + (int64_t)i * 32);
+  uint32_t w[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    w[k] = __hip_atomic_load(&id[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  for (int j = i + 1 + lane; j < n; j += 64)
+    if (copies.lead[j] == i && copies.is_copy(j)) {
+      uint32_t* o = reinterpret_cast<uint32_t*>(digests + (int64_t)j * 32);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) o[k] = w[k];
+    }
+}
+
 // The top of every tensor's tree in one launch, one 64-lane workgroup per
 // (tensor t, fragment i): its m <= 64 x 8 nodes of level v0 are folded in runs
 // of r consecutive ones per lane (r the smallest power of two with m <= 64 r:
@@ -424,15 +508,15 @@ constexpr int64_t kFuseIdMaxGroups = 256;
 __global__ __launch_bounds__(kSubLanes) void hash_tail_kernel(
     const int64_t* __restrict__ table, int64_t stride, int64_t token_bytes, int32_t v0,
     const int64_t* __restrict__ base_lo, const int64_t* __restrict__ base_top,
-    const uint8_t* __restrict__ select, uint32_t want, const uint8_t* __restrict__ in,
-    uint8_t* out, IdShape sh, int32_t* __restrict__ arrived, uint8_t* __restrict__ digests) {
+    int32_t n, HashPass pass, const uint8_t* __restrict__ in, uint8_t* out, IdShape sh,
+    int32_t* __restrict__ arrived, uint8_t* __restrict__ digests) {
   __shared__ uint32_t lds[(1 << (kSubLevels - 1)) * 8][kSubLanes];
   __shared__ __attribute__((aligned(16))) uint32_t vals[kSubLanes * 8];
   __shared__ int32_t seen;
   const int t = blockIdx.x;
   const int i = blockIdx.y;
   const int lane = threadIdx.x;
-  if (select && select[i] != want) return;   // uniform over the workgroup
+  if (!pass.takes(i, n, lane)) return;       // uniform over the workgroup
   const int64_t m0 = chunks_of(table[(int64_t)i * stride] * token_bytes);
   const int64_t m = nodes_at(m0, v0);                  // <= 2^kTailLevels (checked by the host)
   int K = 0;                                           // r = 2^K nodes per lane
@@ -466,6 +550,7 @@ __global__ __launch_bounds__(kSubLanes) void hash_tail_kernel(
   __threadfence();                       // acquire the other workgroups' roots
   fragment_id((uint64_t)table[(int64_t)i * stride], sh, out + base_top[i] * 32,
               digests + (int64_t)i * 32, lane);
+  copy_digest(pass.copies, i, n, digests, lane);
   if (lane == 0) arrived[i] = 0;
 }
 
@@ -473,12 +558,13 @@ __global__ __launch_bounds__(kSubLanes) void hash_tail_kernel(
 // launch to compute it), one workgroup per fragment.
 __global__ __launch_bounds__(64) void hash_final_kernel(
     const int64_t* __restrict__ table, int64_t stride, IdShape sh,
-    const int64_t* __restrict__ base_last, const uint8_t* __restrict__ select, uint32_t want,
+    const int64_t* __restrict__ base_last, int32_t n, HashPass pass,
     const uint8_t* __restrict__ roots, uint8_t* __restrict__ digests) {
   const int i = blockIdx.x;
-  if (select && select[i] != want) return;   // uniform over the workgroup
+  if (!pass.takes(i, n, threadIdx.x)) return;   // uniform over the workgroup
   fragment_id((uint64_t)table[(int64_t)i * stride], sh, roots + base_last[i] * 32,
               digests + (int64_t)i * 32, threadIdx.x);
+  copy_digest(pass.copies, i, n, digests, threadIdx.x);
 }
 
 }  // namespace
@@ -530,7 +616,10 @@ hipError_t launch_hash_prep(const SetDesc& s, const HashLayout& lay, uint8_t* ws
 }
 
 hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8_t* select,
-                            uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream) {
+                            uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
+                            const CopyTables* ct, bool early) {
+  HashPass pass{select, want, ct && early, {ct ? ct->keys : nullptr, ct ? ct->lead : nullptr,
+                                            ct ? ct->differs : nullptr}};
   int64_t* base = reinterpret_cast<int64_t*>(ws + lay.off_tables);
   // the stripes' values are in buf0; each launch reads one buffer and writes the other
   uint8_t* buf[2] = {ws + lay.off_buf0, ws + lay.off_buf1};
@@ -567,7 +656,7 @@ hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8
       ScopedTiming tm(K_HASH_PARENT, stream);
       hipLaunchKernelGGL(hash_tail_kernel, dim3((uint32_t)(2 * s.L), (uint32_t)s.n),
                          dim3(kSubLanes), 0, stream, s.table_dev, s.stride, token_bytes_of(s), v0,
-                         base + v0 * nb1, base + lay.levels * nb1, select, want, buf[launch & 1],
+                         base + v0 * nb1, base + lay.levels * nb1, s.n, pass, buf[launch & 1],
                          buf[(launch + 1) & 1], sh, fuse_id ? arrived : nullptr, digests);
     }
     if ((e = hipGetLastError()) != hipSuccess || fuse_id) return e;
@@ -575,13 +664,14 @@ hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8
   }
   ScopedTiming tm(id_timer, stream);
   hipLaunchKernelGGL(hash_final_kernel, dim3((uint32_t)s.n), dim3(64), 0, stream, s.table_dev,
-                     s.stride, sh, base + lay.levels * nb1, select, want, buf[launch & 1],
+                     s.stride, sh, base + lay.levels * nb1, s.n, pass, buf[launch & 1],
                      digests);
   return hipGetLastError();
 }
 
 hipError_t launch_mask_hash_prep(const SetDesc& s, const HashLayout& lay, const KnormPartials& kp,
-                                 double* keys, uint8_t* mask, uint8_t* ws, hipStream_t stream) {
+                                 double* keys, uint8_t* mask, uint8_t* ws, hipStream_t stream,
+                                 const CopyTables* ct) {
   ScopedTiming tm(K_KEY_MASK, stream);
   // at least n threads (the scans over fragments). Up to 64 fragments the node
   // tables take no scan with barriers, and four waves read the score partials in a
@@ -593,15 +683,30 @@ hipError_t launch_mask_hash_prep(const SetDesc& s, const HashLayout& lay, const 
                      s.stride, token_bytes_of(s), s.L, lay.levels, kp.parts, kp.count, kp.direct,
                      s.H, s.d, keys, mask,
                      reinterpret_cast<int64_t*>(ws + lay.off_tables),
-                     reinterpret_cast<int32_t*>(ws + lay.off_arrived));
+                     reinterpret_cast<int32_t*>(ws + lay.off_arrived), ct ? ct->lead : nullptr,
+                     ct ? ct->differs : nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_copies(const SetDesc& s, const HashLayout& lay, const CopyTables& ct,
+                         hipStream_t stream) {
+  ScopedTiming tm(K_KEY_MASK, stream);
+  const int64_t full = (lay.tasks + (kBlock / 64) - 1) / (kBlock / 64);
+  const int64_t cap = (int64_t)device_cu_count() * 4;
+  hipLaunchKernelGGL(copy_kernel, dim3((uint32_t)(full < cap ? full : cap)), dim3(kBlock), 0,
+                     stream, s.table_dev, s.n, s.stride, token_bytes_of(s), s.L, ct.lead,
+                     ct.differs);
   return hipGetLastError();
 }
 
 hipError_t launch_hash(const SetDesc& s, const HashLayout& lay, const uint8_t* select,
                        uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
-                       bool tables_ready) {
+                       bool tables_ready, const CopyTables* ct) {
   hipError_t e = hipSuccess;
   if (!tables_ready && (e = launch_hash_prep(s, lay, ws, stream)) != hipSuccess) return e;
+  const HashPass pass{select, want, ct != nullptr, {ct ? ct->keys : nullptr,
+                                                    ct ? ct->lead : nullptr,
+                                                    ct ? ct->differs : nullptr}};
   {
     int64_t* base = reinterpret_cast<int64_t*>(ws + lay.off_tables);
     const int64_t nb1 = s.n + 1;
@@ -612,11 +717,10 @@ hipError_t launch_hash(const SetDesc& s, const HashLayout& lay, const uint8_t* s
     hipLaunchKernelGGL(hash_chunk_kernel, dim3((uint32_t)grid), dim3(kBlock), 0, stream,
                        s.table_dev, s.n, s.stride, token_bytes_of(s), lay.stripe_level,
                        base + lay.stripe_level * nb1,
-                       base + (int64_t)(lay.levels + 1) * nb1, lay.tasks, select, want,
-                       ws + lay.off_buf0);
+                       base + (int64_t)(lay.levels + 1) * nb1, lay.tasks, pass, ws + lay.off_buf0);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  return launch_hash_tree(s, lay, select, want, digests, ws, stream);
+  return launch_hash_tree(s, lay, select, want, digests, ws, stream, ct, true);
 }
 
 hipError_t launch_hash_paged(const PagedDesc& p, const HashLayout& lay, const uint8_t* select,

@@ -131,23 +131,38 @@ RenderLayout render_layout(const SetDesc& s);
 // Units of one merged row block (the render grid's x extent).
 int64_t render_units(const SetDesc& s, int64_t T_out);
 
+// Re-deliveries known by their bytes (key_mask.h): tables of n entries in the
+// workspace, in the room of the unit render's source bases, which the fused path
+// does not use.
+struct CopyTables {
+  const double* keys;
+  int32_t* lead;
+  int32_t* differs;
+};
+
 // Launchers (enqueue on `stream`, return the first HIP error).
 // select == nullptr hashes every fragment; otherwise only fragments i with
 // select[i] == want (the other digests are left untouched).
 // tables_ready: the node-base tables are already in ws (launch_mask_hash_prep).
 hipError_t launch_hash(const SetDesc& s, const HashLayout& lay, const uint8_t* select,
                        uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
-                       bool tables_ready = false);
+                       bool tables_ready = false, const CopyTables* ct = nullptr);
+// ct (the pass before the order, after launch_copies): only the Ids the order
+// reads, and their copies'.
+hipError_t launch_copies(const SetDesc& s, const HashLayout& lay, const CopyTables& ct,
+                         hipStream_t stream);
 // launch_equal_key_mask and launch_hash_prep in one launch, after folding the
 // score partials into keys (kp.count > 1).
 hipError_t launch_mask_hash_prep(const SetDesc& s, const HashLayout& lay, const KnormPartials& kp,
-                                 double* keys, uint8_t* mask, uint8_t* ws, hipStream_t stream);
+                                 double* keys, uint8_t* mask, uint8_t* ws, hipStream_t stream,
+                                 const CopyTables* ct = nullptr);
 // The stages of launch_hash: node-base tables, then (after the leaves) the
 // parent levels and the final Id.
 hipError_t launch_hash_prep(const SetDesc& s, const HashLayout& lay, uint8_t* ws,
                             hipStream_t stream);
 hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8_t* select,
-                            uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream);
+                            uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
+                            const CopyTables* ct = nullptr, bool early = false);
 hipError_t launch_equal_key_mask(const SetDesc& s, const double* keys, uint8_t* mask,
                                  hipStream_t stream);
 hipError_t launch_knorm(const SetDesc& s, const KnormLayout& lay, int32_t layer, int64_t tail_len,
@@ -166,7 +181,8 @@ hipError_t launch_order(const SetDesc& s, const double* keys, const uint8_t* dig
 hipError_t launch_order_render_prep(const SetDesc& s, const double* keys, const uint8_t* digests,
                                     int64_t* plan, const RenderLayout& rlay, double base,
                                     int32_t style, int32_t stripe_blocks, const uint8_t* select,
-                                    uint8_t* rws, hipStream_t stream);
+                                    uint8_t* rws, hipStream_t stream,
+                                    const CopyTables* ct = nullptr);
 // Render of a set of distinct fragments, steps 2-5 after the score partials:
 // one workgroup folds the scores (kp.count > 1), orders, and builds the unit
 // render's tables for T_out rows; a plan whose T_out differs (the set held
@@ -192,7 +208,7 @@ hipError_t launch_render_hash(const SetDesc& s, const HashLayout& hlay, const Re
                               const int64_t* plan_dev, double base, int32_t style,
                               const uint8_t* select, uint8_t* digests, void* out, uint8_t* ws,
                               hipStream_t stream, bool tables_ready = false,
-                              bool prep_ready = false);
+                              bool prep_ready = false, const CopyTables* ct = nullptr);
 // Rows [row0, T_out) of every row block are rendered into `out`, whose row
 // blocks are T_cap rows long (row0 = 0, T_cap = T_out: the whole merged cache).
 struct RenderRange {

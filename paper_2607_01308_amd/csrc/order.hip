@@ -50,7 +50,8 @@ __device__ __forceinline__ int cmp_digest(const uint32_t (&a)[8], const uint32_t
 __device__ __forceinline__ void order_body(const int64_t* __restrict__ table, int64_t stride,
                                            int32_t n, const double* __restrict__ keys,
                                            const uint8_t* __restrict__ digests, int32_t dedupe,
-                                           int64_t* __restrict__ plan) {
+                                           int64_t* __restrict__ plan,
+                                           const Copies& copies = Copies{}) {
   __shared__ double s_key[1024];
   __shared__ int64_t s_len[1024];     // by delivery, then by slot
   __shared__ int32_t s_first[1024];   // first delivery with the same digest
@@ -95,13 +96,17 @@ __device__ __forceinline__ void order_body(const int64_t* __restrict__ table, in
     for (int j = 0; j < n; ++j) shared |= (j != tid && s_key[j] == key);
     if (shared) load_digest_be(digests, tid, mine);
   }
+  // copies known by their bytes have no digest yet
+  auto known = [&](int j) { return copies.lead && copies.is_copy(j); };
 
   // Absorption: the first arrival of each content is kept (copies share key,
   // length and digest).
   int first = tid;
   if (live) {
-    for (int j = 0; dedupe && j < tid; ++j) {
-      if (s_key[j] != key || s_len[j] != len) continue;
+    const bool mine_known = known(tid);
+    if (mine_known) first = copies.lead[tid];
+    for (int j = 0; dedupe && !mine_known && j < tid; ++j) {
+      if (s_key[j] != key || s_len[j] != len || known(j)) continue;
       uint32_t other[8];
       load_digest_be(digests, j, other);
       if (cmp_digest(other, mine) == 0) { first = j; break; }
@@ -194,13 +199,25 @@ __global__ __launch_bounds__(1024) void order_render_prep_kernel(
     const uint8_t* __restrict__ digests, int64_t* __restrict__ plan, int32_t d, int32_t ep,
     int32_t style, double base, int32_t stripe_blocks, int64_t tensor_pairs, int64_t token_bytes,
     const uint8_t* __restrict__ select, uint8_t* __restrict__ hsel,
-    int64_t* __restrict__ unit_base, double* __restrict__ angles) {
+    int64_t* __restrict__ unit_base, double* __restrict__ angles, Copies copies) {
   int64_t* l = plan_lds();
-  order_body(table, stride, n, keys, digests, 1, l);
+  order_body(table, stride, n, keys, digests, 1, l, copies);
   __syncthreads();
   write_plan(l, n, plan);
   render_tables(l, n, d, ep, style, base, stripe_blocks, tensor_pairs, token_bytes, select, hsel,
                 unit_base, angles, table, stride, 0, nullptr, nullptr, blockIdx.x, gridDim.x);
+  if (copies.lead && blockIdx.x == 0 && l[CM_PLAN_STATUS] == CM_OK) {
+    // of the deliveries with an equal key, those with no other content among them
+    // were not hashed before the order: the render computes their Ids too
+    __syncthreads();
+    const int s = threadIdx.x;
+    if (s < (int)l[CM_PLAN_NUNIQUE]) {
+      const int i = (int)l[CM_PLAN_HEADER + s];
+      bool needed = false;
+      for (int j = 0; j < n; ++j) needed |= copies.ties(i, j);
+      if (!needed) hsel[i] = 0;
+    }
+  }
 }
 
 // Steps 2-5 of a set render before the render itself: the last levels of the
@@ -283,7 +300,7 @@ hipError_t launch_order(const SetDesc& s, const double* keys, const uint8_t* dig
 hipError_t launch_order_render_prep(const SetDesc& s, const double* keys, const uint8_t* digests,
                                     int64_t* plan, const RenderLayout& rlay, double base,
                                     int32_t style, int32_t stripe_blocks, const uint8_t* select,
-                                    uint8_t* rws, hipStream_t stream) {
+                                    uint8_t* rws, hipStream_t stream, const CopyTables* ct) {
   ScopedTiming tm(K_ORDER, stream);
   // a workgroup of at least n threads (one per delivery); an angle pair per thread
   const int threads = order_threads(s.n);
@@ -293,7 +310,9 @@ hipError_t launch_order_render_prep(const SetDesc& s, const double* keys, const 
                      stripe_blocks, (int64_t)s.L, token_bytes_of(s), select,
                      select ? rws + rlay.off_hsel : nullptr,
                      reinterpret_cast<int64_t*>(rws + rlay.off_tiles),
-                     reinterpret_cast<double*>(rws + rlay.off_angles));
+                     reinterpret_cast<double*>(rws + rlay.off_angles),
+                     Copies{ct ? ct->keys : nullptr, ct ? ct->lead : nullptr,
+                            ct ? ct->differs : nullptr});
   return hipGetLastError();
 }
 

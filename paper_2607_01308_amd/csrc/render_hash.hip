@@ -615,7 +615,8 @@ __host__ inline void dispatch_row(int64_t row_bytes, Go&& go) {
 hipError_t launch_render_hash(const SetDesc& s, const HashLayout& hlay, const RenderLayout& rlay,
                               const int64_t* plan_dev, double base, int32_t style,
                               const uint8_t* select, uint8_t* digests, void* out, uint8_t* ws,
-                              hipStream_t stream, bool tables_ready, bool prep_ready) {
+                              hipStream_t stream, bool tables_ready, bool prep_ready,
+                              const CopyTables* ct) {
   uint8_t* hws = ws;
   uint8_t* rws = ws + align_up(hlay.bytes, kWsAlign);
   hipError_t e = hipSuccess;
@@ -671,7 +672,7 @@ hipError_t launch_render_hash(const SetDesc& s, const HashLayout& hlay, const Re
     dispatch_row(s.row_bytes, go);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  return launch_hash_tree(s, hlay, hsel, 0, digests, hws, stream);
+  return launch_hash_tree(s, hlay, hsel, 0, digests, hws, stream, ct);
 }
 
 hipError_t launch_paged_render_hash(const PagedDesc& p, const HashLayout& hlay,

@@ -1,0 +1,71 @@
+"""GPU: re-deliveries known by their bytes inside the one-call path.
+
+From 256 MiB of deliveries on, the one-call path compares deliveries of equal
+score and length instead of hashing each of them first. Groups where every form
+meets: copies, a damaged copy (one bit, in the last bytes of the last tensor), equal
+K with another V (with copies of their own, which are no copies of the group's
+first), and an equal score at another length. The result must be the serial
+pipeline's, which hashes every delivery and never compares, bit for bit: Ids, plan,
+merged cache; also replayed from a graph."""
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+import paper_2607_01308_amd as cm
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    yield
+    torch.cuda.synchronize()
+
+
+def _clone(c):
+    return tuple((k.clone(), v.clone()) for k, v in c)
+
+
+def _groups(dtype, T):
+    d = 128 if dtype == "bfloat16" else 64
+    w = synth.custom("copies", L=8, H=8, d=d, dtype=dtype, lengths=(T, T, T + 100, T + 13),
+                     shared_k=((0, 1),), seed=T)
+    a, b, e, z = synth.make_fragments(w, device="cuda")
+    for (ka, _), (ke, _) in zip(a, e):
+        ke[:, :, -T:] = ka                       # a's score, another length
+    flipped = _clone(a)
+    flipped[-1][1].view(torch.int32).view(-1)[-1] ^= 1
+    return [a, b, _clone(a), flipped, _clone(b), _clone(a), e, _clone(e), _clone(flipped), z]
+
+
+@pytest.mark.parametrize("dtype,T,seed", [("bfloat16", 1201, 0), ("bfloat16", 1201, 1),
+                                          ("bfloat16", 1280, 2), ("float32", 1203, 3)])
+def test_copies_against_the_serial_pipeline(dtype, T, seed):
+    dl = _groups(dtype, T)
+    dl = [dl[i] for i in np.random.default_rng(seed).permutation(len(dl))]
+    batch = cm.FragmentBatch(dl)
+    assert sum(batch.fragment_bytes(i) for i in range(batch.n)) > 256 << 20
+    want = cm.render_deliveries(batch, 3, 1e6, pipeline="serial")
+    got = cm.render_deliveries(batch, 3, 1e6)
+    graph = cm.RenderGraph(batch, 3, 1e6)
+    for r in (got, graph.replay(), graph.replay()):
+        assert r.digests == want.digests
+        assert r.n_unique == 5
+        assert np.array_equal(r.plan, want.plan)
+        assert torch.equal(r.merged.view(torch.int16), want.merged.view(torch.int16))
+    graph.close()
+
+
+def test_only_copies():
+    """Every delivery of a key is the same fragment: no digest is read before the order."""
+    w = synth.custom("same", L=8, H=8, d=128, lengths=(3000, 2999), seed=5)
+    a, b = synth.make_fragments(w, device="cuda")
+    batch = cm.FragmentBatch([b, a, _clone(a), _clone(b), _clone(a)])
+    want = cm.render_deliveries(batch, 3, 1e6, pipeline="serial")
+    got = cm.render_deliveries(batch, 3, 1e6)
+    assert got.digests == want.digests and np.array_equal(got.plan, want.plan)
+    assert torch.equal(got.merged.view(torch.int16), want.merged.view(torch.int16))
