@@ -120,7 +120,9 @@ static int64_t line_check(int32_t n_u, const int64_t* T, const int64_t* off, int
     const int64_t bytes = (int64_t)H * T[s] * RB;
     const int64_t gap = (T_out - T[s]) << rb_shift;
     const float inv_T = 1.0f / (float)T[s];
-    for (int64_t sidx = 0; (sidx + 1) * 65536 <= bytes; ++sidx) {
+    for (int64_t sidx = 0; sidx * 65536 < bytes; ++sidx) {
+      // (a last stripe's bytes have the same offsets, as far as they go)
+      const int64_t end = bytes - sidx * 65536 < 65536 ? bytes - sidx * 65536 : 65536;
       const cm::FusedStripe f = cm::fused_stripe(sidx, rb_shift, T[s], T_out, off[s]);
       std::vector<uint8_t> seen(4096, 0);
       for (int k = 0; k < 8; ++k)
@@ -128,6 +130,7 @@ static int64_t line_check(int32_t n_u, const int64_t* T, const int64_t* off, int
           for (int lane = 0; lane < 64; ++lane) {
             const uint32_t o = cm::fused_line_step(k, j) + cm::fused_line_lane(lane);
             if (o % 16 != 0 || o > 65536 - 16) { ++bad; continue; }
+            if (o >= end) continue;
             if (seen[o >> 4]++) ++bad;
             const int64_t b = sidx * 65536 + o;              // byte of the tensor
             const int64_t r = b >> rb_shift;
@@ -140,8 +143,8 @@ static int64_t line_check(int32_t n_u, const int64_t* T, const int64_t* off, int
                 cm::fused_line_col<RB>(k, lane) != (int)(o & (RB - 1)))
               ++bad;
           }
-      for (uint8_t c : seen)
-        if (c != 1) ++bad;
+      for (size_t c = 0; c < seen.size(); ++c)
+        if (seen[c] != ((int64_t)c * 16 < end ? 1 : 0)) ++bad;
     }
   }
   return bad;
