@@ -8,6 +8,8 @@
 // differs[i]. A delivery is then a copy, or one whose digest the order reads if
 // another of its key is no copy either, or one whose Id the render computes.
 // (lead == nullptr: every delivery with an equal key is hashed before the order.)
+// With a non-finite score in the set nothing is rendered, so nothing is left to the
+// render: no delivery counts as a copy, and all with an equal key are hashed.
 #pragma once
 
 #include "internal.h"
@@ -44,7 +46,7 @@ __device__ __forceinline__ void equal_key_mask_body(int32_t n, const double* __r
     key = keys[tid];
     s_key[tid] = key;
   }
-  __syncthreads();
+  const bool renders = !__syncthreads_or(tid < n && !isfinite(key));
   if (tid < n) {
     bool shared = false;
     for (int j = 0; j < n; ++j) shared |= (j != tid && s_key[j] == key);
@@ -52,7 +54,7 @@ __device__ __forceinline__ void equal_key_mask_body(int32_t n, const double* __r
     if (lead) {
       const int64_t len = table[(int64_t)tid * stride];
       int l = tid;
-      for (int j = 0; j < tid && shared; ++j)
+      for (int j = 0; renders && shared && j < tid; ++j)
         if (s_key[j] == key && table[(int64_t)j * stride] == len) {
           l = j;
           break;

@@ -6,7 +6,9 @@ meets: copies, a damaged copy (one bit, in the last bytes of the last tensor), e
 K with another V (with copies of their own, which are no copies of the group's
 first), and an equal score at another length. The result must be the serial
 pipeline's, which hashes every delivery and never compares, bit for bit: Ids, plan,
-merged cache; also replayed from a graph."""
+merged cache; also replayed from a graph. With a non-finite score in the set nothing
+is rendered, and the Ids of the deliveries with an equal score are written all the
+same."""
 
 import numpy as np
 import pytest
@@ -14,6 +16,7 @@ import torch
 
 import synth
 import paper_2607_01308_amd as cm
+from paper_2607_01308_amd import _cabi as C
 
 pytestmark = pytest.mark.gpu
 
@@ -69,3 +72,29 @@ def test_only_copies():
     got = cm.render_deliveries(batch, 3, 1e6)
     assert got.digests == want.digests and np.array_equal(got.plan, want.plan)
     assert torch.equal(got.merged.view(torch.int16), want.merged.view(torch.int16))
+
+
+def test_colliding_ids_are_written_beside_a_non_finite_score():
+    dl = _groups("bfloat16", 1201)
+    bad = _clone(dl[-1])
+    bad[3][0][0, 0, -1, 0] = float("nan")
+    dl.insert(4, bad)
+    dl.append(_clone(dl[-1]))                    # the only copies among those that collide
+    batch = cm.FragmentBatch(dl)
+    assert sum(batch.fragment_bytes(i) for i in range(batch.n)) > 256 << 20
+    n, T = batch.n, sum(batch.lengths)
+    keys = torch.empty(n, dtype=torch.float64, device="cuda")
+    mask = torch.empty(n, dtype=torch.uint8, device="cuda")
+    digests = torch.full((n, 32), 0xCD, dtype=torch.uint8, device="cuda")
+    plan = torch.empty(cm.plan_elems(n), dtype=torch.int64, device="cuda")
+    out = torch.full((batch.L * 2 * batch.H * T * batch.d,), 7.0, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(cm.workspace_size(batch), dtype=torch.uint8, device="cuda")
+    cm.render_deliveries_async(batch, 3, min(batch.lengths), 1e6, "half", keys, mask, digests, plan,
+                               out, T, ws)
+    assert int(plan[C.PLAN_STATUS]) == C.CM_ENONFINITE
+    ids = cm.fragment_ids(dl)
+    got = [bytes(r) for r in digests.cpu().numpy()]
+    collide = mask.cpu().tolist()
+    assert collide == [1, 1, 1, 1, 0, 1, 1, 1, 1, 1, 1, 1]
+    assert got == [f if c else b"\xcd" * 32 for f, c in zip(ids, collide)]
+    assert bool((out == 7.0).all())
