@@ -7,6 +7,7 @@
 // pieces 1 KiB apart (one column per lane, so the lane's angles are loaded once
 // when the page comes from one slot). A prep pass resolves each fresh page to
 // its slot and the one or two fragment pages its rows come from.
+#include "paged_plan.h"
 #include "rotate.h"
 
 namespace cm {
@@ -181,26 +182,13 @@ __global__ __launch_bounds__(1024) void paged_tables_kernel(
   __shared__ int64_t s_first[CM_MAX_FRAGMENTS];
   __shared__ int64_t scan[1024];
   const int tid = threadIdx.x, nt = blockDim.x;
-  auto refuse = [&](int64_t pages, int64_t status) {
-    for (int i = tid; i < n; i += nt) hsel[i] = 1;
-    if (tid == 0) {
-      *n_fresh = pages;
-      *task_total = 0;
-      plan[CM_PLAN_STATUS] = status;
-    }
-  };
-  if (plan[CM_PLAN_STATUS] != CM_OK) {
-    if (tid == 0) *n_fresh = 0;
+  if (!paged_plan_usable(plan, n, b_shift, nbo_cap, n_fresh, task_total, hsel, tid, nt,
+                         [] { __syncthreads(); }))
     return;
-  }
   const int n_u = (int)plan[CM_PLAN_NUNIQUE];
   const int64_t T_out = plan[CM_PLAN_TOUT];
   const int64_t B = (int64_t)1 << b_shift;
   const int64_t nbo = (T_out + B - 1) >> b_shift;
-  if (n_u < 1 || n_u > n || nbo > nbo_cap) {     // not a plan of this set (checked on the
-    refuse(0, CM_ESHAPE);                        // host for every other entry point)
-    return;
-  }
   for (int s = tid; s < n_u; s += nt) {
     s_off[s] = plan[CM_PLAN_HEADER + n + s];
     s_len[s] = plan[CM_PLAN_HEADER + 2 * (int64_t)n + s];
@@ -249,7 +237,7 @@ __global__ __launch_bounds__(1024) void paged_tables_kernel(
   }
   const int64_t total = scan[nt - 1];
   if (total > n_free) {
-    refuse(total, CM_EINVAL);
+    paged_refuse(plan, n, total, CM_EINVAL, n_fresh, task_total, hsel, tid, nt);
     return;
   }
   int64_t next = scan[tid] - cnt;

@@ -6,14 +6,19 @@
 // and walks the address maps of the fused kernel on dense and on paged storage
 // (fused_geometry.h) and of the unit render (render_geometry.h), the same
 // sources the kernels use, over every task, unit, lane, row and piece of a
-// launch. Test support only.
+// launch; and runs a workgroup's threads through the paged tables' guard
+// (paged_plan.h). Test support only.
 #include <stdint.h>
 #include <string.h>
 
+#include <condition_variable>
+#include <mutex>
+#include <thread>
 #include <vector>
 
 #include "blake3.h"
 #include "fused_geometry.h"
+#include "paged_plan.h"
 #include "render_geometry.h"
 
 namespace {
@@ -269,6 +274,52 @@ int64_t hc_paged_fused_check(int32_t n_u, const int64_t* T, const int64_t* off,
   for (uint8_t z : seen)
     if (!z) ++bad;
   return bad;
+}
+
+// The guard of the paged table kernel (paged_plan_usable) by a workgroup of nt
+// threads in the worst order: each thread runs as far as the next barrier, or to
+// its end, before the next thread starts. plan, n_fresh, task_total and hsel as the
+// kernel has them. Returns how many threads found the plan usable, or -1 if the
+// threads did not all meet at the same barriers.
+int64_t hc_paged_guard(int64_t* plan, int32_t n, int32_t b_shift, int64_t nbo_cap,
+                       int64_t* n_fresh, int64_t* task_total, uint8_t* hsel, int32_t nt) {
+  std::mutex mu;
+  std::condition_variable cv;
+  int stopped = 0, finished = 0, passed = 0;   // threads at a barrier, ended; barriers released
+  int64_t usable = 0;
+  std::vector<std::thread> threads;
+  for (int t = 0; t < nt; ++t) {
+    threads.emplace_back([&, t] {
+      auto sync = [&] {
+        std::unique_lock<std::mutex> lk(mu);
+        const int now = passed;
+        ++stopped;
+        cv.notify_all();
+        cv.wait(lk, [&] { return passed != now; });
+      };
+      const bool ok = cm::paged_plan_usable(plan, n, b_shift, nbo_cap, n_fresh, task_total, hsel,
+                                            t, nt, sync);
+      std::lock_guard<std::mutex> lk(mu);
+      ++finished;
+      usable += ok ? 1 : 0;
+      cv.notify_all();
+    });
+    std::unique_lock<std::mutex> lk(mu);
+    cv.wait(lk, [&] { return stopped + finished == t + 1; });
+  }
+  bool uniform = true;
+  std::unique_lock<std::mutex> lk(mu);
+  while (finished < nt) {
+    uniform = uniform && finished == 0;
+    stopped = 0;
+    ++passed;
+    const int ended = finished;
+    cv.notify_all();
+    cv.wait(lk, [&] { return stopped + finished == nt && (stopped > 0 || finished > ended); });
+  }
+  lk.unlock();
+  for (std::thread& t : threads) t.join();
+  return uniform ? usable : -1;
 }
 
 }  // extern "C"

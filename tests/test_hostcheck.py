@@ -1,8 +1,9 @@
 """The library's BLAKE3 code (csrc/blake3.h), compiled for the host by the
 test harness tests/native/hostcheck.hip, against the published BLAKE3 test
 vectors and the oracle, with the chunk counters, flags and parent nodes the GPU
-path uses; and the compiler's single-step fp64 -> bf16 conversion used by the
-render kernel, against the oracle."""
+path uses; the compiler's single-step fp64 -> bf16 conversion used by the
+render kernel, against the oracle; and the paged table kernel's guard with its
+threads run one after the other."""
 
 import ctypes
 import os
@@ -11,6 +12,7 @@ import numpy as np
 import pytest
 
 import oracle
+from paper_2607_01308_amd import _cabi as C
 
 LIB = os.path.join(os.path.dirname(os.path.abspath(__file__)), "native", "libcm_hostcheck.so")
 
@@ -92,3 +94,29 @@ def test_single_step_bf16_conversion(hc):
     y = np.zeros(x.size, np.uint16)
     hc.hc_f64_to_bf16(x.ctypes.data, y.ctypes.data, x.size)
     assert np.array_equal(y, oracle.f64_to_bf16_bits(x))
+
+
+@pytest.mark.parametrize("status,n_unique,T_out,want,fresh,refused", [
+    (0, 3, 100, True, -5, False),               # a plan of the set
+    (0, 0, 100, False, 0, True), (0, 201, 100, False, 0, True),
+    (0, 3, 1601, False, 0, True),               # more blocks than the tables hold
+    (C.CM_ENONFINITE, 0, 0, False, 0, False),                 # already an error: left as it is
+])
+def test_paged_plan_guard_by_every_thread(hc, status, n_unique, T_out, want, fresh, refused):
+    """Every thread of the workgroup takes the same way out of the guard, whichever
+    comes first: a refused plan has no Id and no task left (with one thread writing
+    the plan's status before another has read it, the rest of the Ids stay)."""
+    n, nt, cap = 200, 64, 100
+    plan = np.array([status, n, n_unique, T_out] + [-1] * (4 * n), np.int64)
+    fresh_out, tasks = np.full(1, -5, np.int64), np.full(1, 77, np.int64)
+    hsel = np.zeros(n, np.uint8)
+    hc.hc_paged_guard.restype = ctypes.c_int64
+    P = ctypes.c_void_p
+    hc.hc_paged_guard.argtypes = [P, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, P, P, P,
+                                  ctypes.c_int32]
+    usable = hc.hc_paged_guard(plan.ctypes.data, n, 4, cap, fresh_out.ctypes.data,
+                               tasks.ctypes.data, hsel.ctypes.data, nt)
+    assert usable == (nt if want else 0)
+    assert fresh_out[0] == fresh
+    assert tasks[0] == (0 if refused else 77) and hsel.tolist() == [int(refused)] * n
+    assert plan[C.PLAN_STATUS] == (C.CM_ESHAPE if refused else status)
