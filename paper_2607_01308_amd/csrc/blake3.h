@@ -147,24 +147,33 @@ __host__ __device__ __forceinline__ void b3_compress(B3Cv& s, const uint32_t (&m
   CM_B3_RUN_XOR(4, 8) CM_B3_RUN_XOR(5, 9) CM_B3_RUN_XOR(6, 10) CM_B3_RUN_XOR(7, 11)           \
   CM_B3_PRIO(PB)                                                                              \
   CM_B3_RUN_ROT(4, RB) CM_B3_RUN_ROT(5, RB) CM_B3_RUN_ROT(6, RB) CM_B3_RUN_ROT(7, RB)
+// Early clobber: the state is written before the second half step's words are read,
+// so no word may share a register with a state word of the same value.
 #define CM_B3_STEP_OPERANDS                                                                     \
-  : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3), "+v"(b0), "+v"(b1), "+v"(b2), "+v"(b3), "+v"(c0),   \
-    "+v"(c1), "+v"(c2), "+v"(c3), "+v"(d0), "+v"(d1), "+v"(d2), "+v"(d3)                        \
+  : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3), "+&v"(b0), "+&v"(b1), "+&v"(b2), "+&v"(b3),     \
+    "+&v"(c0), "+&v"(c1), "+&v"(c2), "+&v"(c3), "+&v"(d0), "+&v"(d1), "+&v"(d2), "+&v"(d3)      \
   : "v"(x0), "v"(y0), "v"(x1), "v"(y1), "v"(x2), "v"(y2), "v"(x3), "v"(y3)
 
-template <int LEVELS>
+// LAST: the compression's last step, which leaves the wave at priority 0 (in the same
+// asm, so that nothing orders the reset before the runs).
+template <int LEVELS, bool LAST>
 __device__ __forceinline__ void b3_step_paired(
     uint32_t& a0, uint32_t& a1, uint32_t& a2, uint32_t& a3, uint32_t& b0, uint32_t& b1,
     uint32_t& b2, uint32_t& b3, uint32_t& c0, uint32_t& c1, uint32_t& c2, uint32_t& c3,
     uint32_t& d0, uint32_t& d1, uint32_t& d2, uint32_t& d3, uint32_t x0, uint32_t y0, uint32_t x1,
     uint32_t y1, uint32_t x2, uint32_t y2, uint32_t x3, uint32_t y3) {
-  if constexpr (LEVELS == 0) {
-    asm(CM_B3_HALF_STEP(2, 1, 1, 0, 3, 16, 18, 20, 22, 16, 12)
-        CM_B3_HALF_STEP(2, 1, 1, 0, 3, 17, 19, 21, 23, 8, 7) CM_B3_STEP_OPERANDS);
-  } else {
-    asm(CM_B3_HALF_STEP(2, 0, 3, 1, 3, 16, 18, 20, 22, 16, 12)
-        CM_B3_HALF_STEP(2, 0, 3, 1, 3, 17, 19, 21, 23, 8, 7) CM_B3_STEP_OPERANDS);
-  }
+#define CM_B3_STEP(END)                                                                         \
+  do {                                                                                        \
+    if constexpr (LEVELS == 0)                                                                \
+      asm(CM_B3_HALF_STEP(2, 1, 1, 0, 3, 16, 18, 20, 22, 16, 12)                              \
+          CM_B3_HALF_STEP(2, 1, 1, 0, 3, 17, 19, 21, 23, 8, 7) END CM_B3_STEP_OPERANDS);      \
+    else                                                                                      \
+      asm(CM_B3_HALF_STEP(2, 0, 3, 1, 3, 16, 18, 20, 22, 16, 12)                              \
+          CM_B3_HALF_STEP(2, 0, 3, 1, 3, 17, 19, 21, 23, 8, 7) END CM_B3_STEP_OPERANDS);      \
+  } while (0)
+  if constexpr (LAST) CM_B3_STEP(CM_B3_PRIO(0));
+  else CM_B3_STEP("");
+#undef CM_B3_STEP
 }
 
 #undef CM_B3_STEP_OPERANDS
@@ -175,12 +184,14 @@ __device__ __forceinline__ void b3_step_paired(
 #undef CM_B3_RUN_XOR
 #undef CM_B3_RUN_ADD3
 
-#define CM_B3P_ROUND(p0, p1, p2, p3, p4, p5, p6, p7, p8, p9, p10, p11, p12, p13, p14, p15)      \
+#define CM_B3P_ROUND(LAST, p0, p1, p2, p3, p4, p5, p6, p7, p8, p9, p10, p11, p12, p13, p14, p15) \
   do {                                                                                        \
-    b3_step_paired<LEVELS>(v0, v1, v2, v3, v4, v5, v6, v7, v8, v9, v10, v11, v12, v13, v14,    \
-                           v15, m[p0], m[p1], m[p2], m[p3], m[p4], m[p5], m[p6], m[p7]);       \
-    b3_step_paired<LEVELS>(v0, v1, v2, v3, v5, v6, v7, v4, v10, v11, v8, v9, v15, v12, v13,    \
-                           v14, m[p8], m[p9], m[p10], m[p11], m[p12], m[p13], m[p14], m[p15]); \
+    b3_step_paired<LEVELS, false>(v0, v1, v2, v3, v4, v5, v6, v7, v8, v9, v10, v11, v12, v13,  \
+                                  v14, v15, m[p0], m[p1], m[p2], m[p3], m[p4], m[p5], m[p6],   \
+                                  m[p7]);                                                     \
+    b3_step_paired<LEVELS, LAST>(v0, v1, v2, v3, v5, v6, v7, v4, v10, v11, v8, v9, v15, v12,   \
+                                 v13, v14, m[p8], m[p9], m[p10], m[p11], m[p12], m[p13],       \
+                                 m[p14], m[p15]);                                             \
   } while (0)
 #endif
 
@@ -196,14 +207,13 @@ __device__ __forceinline__ void b3_compress_paired(B3Cv& s, const uint32_t (&m)[
   uint32_t v8 = CM_B3_IV0, v9 = CM_B3_IV1, v10 = CM_B3_IV2, v11 = CM_B3_IV3;
   uint32_t v12 = (uint32_t)counter, v13 = (uint32_t)(counter >> 32);
   uint32_t v14 = block_len, v15 = flags;
-  CM_B3P_ROUND(0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-  CM_B3P_ROUND(2, 6, 3, 10, 7, 0, 4, 13, 1, 11, 12, 5, 9, 14, 15, 8);
-  CM_B3P_ROUND(3, 4, 10, 12, 13, 2, 7, 14, 6, 5, 9, 0, 11, 15, 8, 1);
-  CM_B3P_ROUND(10, 7, 12, 9, 14, 3, 13, 15, 4, 0, 11, 2, 5, 8, 1, 6);
-  CM_B3P_ROUND(12, 13, 9, 11, 15, 10, 14, 8, 7, 2, 5, 3, 0, 1, 6, 4);
-  CM_B3P_ROUND(9, 14, 11, 5, 8, 12, 15, 1, 13, 3, 0, 10, 2, 6, 4, 7);
-  CM_B3P_ROUND(11, 15, 5, 0, 1, 9, 8, 6, 14, 10, 2, 12, 3, 4, 7, 13);
-  __builtin_amdgcn_s_setprio(0);
+  CM_B3P_ROUND(false, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+  CM_B3P_ROUND(false, 2, 6, 3, 10, 7, 0, 4, 13, 1, 11, 12, 5, 9, 14, 15, 8);
+  CM_B3P_ROUND(false, 3, 4, 10, 12, 13, 2, 7, 14, 6, 5, 9, 0, 11, 15, 8, 1);
+  CM_B3P_ROUND(false, 10, 7, 12, 9, 14, 3, 13, 15, 4, 0, 11, 2, 5, 8, 1, 6);
+  CM_B3P_ROUND(false, 12, 13, 9, 11, 15, 10, 14, 8, 7, 2, 5, 3, 0, 1, 6, 4);
+  CM_B3P_ROUND(false, 9, 14, 11, 5, 8, 12, 15, 1, 13, 3, 0, 10, 2, 6, 4, 7);
+  CM_B3P_ROUND(true, 11, 15, 5, 0, 1, 9, 8, 6, 14, 10, 2, 12, 3, 4, 7, 13);
   s.h[0] = v0 ^ v8;
   s.h[1] = v1 ^ v9;
   s.h[2] = v2 ^ v10;
