@@ -576,6 +576,9 @@ int32_t cm_render_merge_hash(const cm_fragset* set, const int64_t* plan_dev,
 
 namespace {
 
+// Bytes of deliveries from which re-deliveries are found by comparison.
+constexpr int64_t kCopyBytes = (int64_t)256 << 20;
+
 // Steps 1-5 of cm_render_deliveries after its argument checks. The workspace is
 // the caller's (workspace_bytes its size) or, with fixed_scratch, this device's
 // copy of `scratch`, once the set's need is known to fit it.
@@ -630,11 +633,14 @@ int32_t render_deliveries_common(const cm_fragset* set, int32_t routing_layer, i
   const cm::HashLayout hlay = cm::hash_layout(s);
   const cm::RenderLayout rlay = cm::render_layout(s);
   // re-deliveries by their bytes, from 256 MiB of deliveries on: comparing them
-  // takes a launch (about 4 us when no scores are equal), hashing 256 MiB 70 us
+  // takes a launch (about 4 us when no scores are equal), hashing 256 MiB 70 us.
+  // (Bytes, not stripes: a deep model's short tensors are many stripes and little
+  // to hash.)
   uint8_t* rws = ws + cm::align_up(hlay.bytes, cm::kWsAlign);
   int32_t* lead = reinterpret_cast<int32_t*>(rws + rlay.off_src_base);
   const cm::CopyTables tables{keys_dev, lead, lead + s.n};
-  const cm::CopyTables* ct = s.n > 1 && hlay.tasks >= 4096 ? &tables : nullptr;
+  const bool large = T_all * cm::token_bytes_of(s) * 2 * s.L >= kCopyBytes;
+  const cm::CopyTables* ct = s.n > 1 && large ? &tables : nullptr;
   // the last score levels, the key mask and the hash trees' node tables in one
   // launch (the tables depend only on the lengths); it reads the score partials
   // before it writes over them

@@ -98,3 +98,30 @@ def test_colliding_ids_are_written_beside_a_non_finite_score():
     assert collide == [1, 1, 1, 1, 0, 1, 1, 1, 1, 1, 1, 1]
     assert got == [f if c else b"\xcd" * 32 for f, c in zip(ids, collide)]
     assert bool((out == 7.0).all())
+
+
+def _many(n, copies, T, seed, L=2):
+    """n deliveries of L x H = 8 x T x d = 64, `copies` of them drawn from the others."""
+    w = synth.custom("many", L=L, H=8, d=64, lengths=(T,) * (n - copies), routing_layer=1, seed=seed)
+    base = list(synth.make_fragments(w, device="cuda"))
+    rng = np.random.default_rng(seed)
+    dl = base + [_clone(base[int(i)]) for i in rng.integers(0, len(base), copies)]
+    return [dl[i] for i in rng.permutation(n)]
+
+
+@pytest.mark.parametrize("n,T,compares", [(1024, 8, 0), (128, 512, 1), (127, 512, 0)])
+def test_deliveries_are_compared_from_256_mib_on(n, T, compares):
+    """4096 stripes of little (33 MB) and of 64 KiB (256 MiB), and one delivery less."""
+    batch = cm.FragmentBatch(_many(n, 3, T, seed=n))
+    assert (sum(batch.fragment_bytes(i) for i in range(n)) >= 256 << 20) == bool(compares)
+    cm.timing_reset()
+    cm.timing_enable(True)
+    try:
+        res = cm.render_deliveries(batch, 1, 1e6)
+        torch.cuda.synchronize()
+        launches = cm.timing_query("key_mask")[1]
+    finally:
+        cm.timing_enable(False)
+        cm.timing_reset()
+    assert launches == 1 + compares
+    assert res.n_unique == n - 3
