@@ -637,8 +637,7 @@ int32_t render_deliveries_common(const cm_fragset* set, int32_t routing_layer, i
   // (Bytes, not stripes: a deep model's short tensors are many stripes and little
   // to hash.)
   uint8_t* rws = ws + cm::align_up(hlay.bytes, cm::kWsAlign);
-  int32_t* lead = reinterpret_cast<int32_t*>(rws + rlay.off_src_base);
-  const cm::CopyTables tables{keys_dev, lead, lead + s.n};
+  const cm::CopyTables tables = cm::copy_tables(keys_dev, rws + rlay.off_src_base, s.n);
   const bool large = T_all * cm::token_bytes_of(s) * 2 * s.L >= kCopyBytes;
   const cm::CopyTables* ct = s.n > 1 && large ? &tables : nullptr;
   // the last score levels, the key mask and the hash trees' node tables in one

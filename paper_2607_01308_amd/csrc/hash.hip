@@ -113,9 +113,9 @@ __global__ __launch_bounds__(1024) void mask_hash_prep_kernel(
     const int64_t* __restrict__ table, int32_t n, int64_t stride, int64_t token_bytes, int32_t L,
     int32_t levels, const double* parts, int64_t count, KnormDirect kd, int32_t H, int32_t d,
     double* keys, uint8_t* __restrict__ mask, int64_t* base, int32_t* __restrict__ arrived,
-    int32_t* lead, int32_t* differs) {
+    int32_t* lead, int32_t* differs, int32_t* end) {
   knorm_finish(table, stride, n, H, d, kd, parts, count, keys);
-  equal_key_mask_body(n, keys, mask, table, stride, lead, differs);
+  equal_key_mask_body(n, keys, mask, table, stride, token_bytes, L, lead, differs, end);
   hash_tables(table, n, stride, token_bytes, L, levels, base, arrived);
 }
 
@@ -125,48 +125,49 @@ __global__ __launch_bounds__(1024) void mask_hash_prep_kernel(
 // deliveries with equal keys, six of ten of them copies: hashing them and their
 // trees took 340 us, and the whole path 721; with this it takes 628). A wave
 // takes 64 KiB at a time, 8 KiB of each side in flight, and leaves a delivery
-// that is known to differ.
+// that is known to differ. The stripes of all compared deliveries are one range, so
+// that many small ones fill the chip as one large one does.
 __global__ __launch_bounds__(kBlock) void copy_kernel(const int64_t* __restrict__ table, int32_t n,
                                                       int64_t stride, int64_t token_bytes,
-                                                      int32_t L, const int32_t* __restrict__ lead,
+                                                      const int32_t* __restrict__ lead,
+                                                      const int32_t* __restrict__ end,
                                                       int32_t* differs) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wave
   const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
-  const int64_t first = (int64_t)blockIdx.x * (kBlock / 64) + wave;
-  for (int i = 0; i < n; ++i) {
+  const int64_t total = end[n - 1];
+  for (int64_t task = (int64_t)blockIdx.x * (kBlock / 64) + wave; task < total; task += waves) {
+    int64_t local;
+    const int i = copy_task(end, n, task, &local);
+    if (__hip_atomic_load(&differs[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) continue;
     const int l = lead[i];
-    if (l == i) continue;
     const int64_t bytes = table[(int64_t)i * stride] * token_bytes;
     const int64_t stripes = stripes_of(bytes);
-    for (int64_t task = first; task < 2 * L * stripes; task += waves) {
-      if (__hip_atomic_load(&differs[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
-      const int64_t t = task / stripes;
-      const int64_t b0 = (task - t * stripes) << 16;
-      const int64_t len = bytes - b0 < 65536 ? bytes - b0 : 65536;
-      const uint8_t* a = reinterpret_cast<const uint8_t*>(table[(int64_t)i * stride + 1 + t]) + b0;
-      const uint8_t* b = reinterpret_cast<const uint8_t*>(table[(int64_t)l * stride + 1 + t]) + b0;
-      bool other = false;
-      for (int64_t o = 0; o < len && !other; o += 8192) {
-        u32x4 x[8], y[8];
+    const int64_t t = local / stripes;
+    const int64_t b0 = (local - t * stripes) << 16;
+    const int64_t len = bytes - b0 < 65536 ? bytes - b0 : 65536;
+    const uint8_t* a = reinterpret_cast<const uint8_t*>(table[(int64_t)i * stride + 1 + t]) + b0;
+    const uint8_t* b = reinterpret_cast<const uint8_t*>(table[(int64_t)l * stride + 1 + t]) + b0;
+    bool other = false;
+    for (int64_t o = 0; o < len && !other; o += 8192) {
+      u32x4 x[8], y[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int64_t c = o + 1024 * k + lane * 16;
-          x[k] = y[k] = u32x4{0u, 0u, 0u, 0u};
-          if (c < len) {
-            x[k] = *global_ptr<u32x4>(a + c);
-            y[k] = *global_ptr<u32x4>(b + c);
-          }
+      for (int k = 0; k < 8; ++k) {
+        const int64_t c = o + 1024 * k + lane * 16;
+        x[k] = y[k] = u32x4{0u, 0u, 0u, 0u};
+        if (c < len) {
+          x[k] = *global_ptr<u32x4>(a + c);
+          y[k] = *global_ptr<u32x4>(b + c);
         }
-        uint32_t d = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-          d |= (x[k][0] ^ y[k][0]) | (x[k][1] ^ y[k][1]) | (x[k][2] ^ y[k][2]) | (x[k][3] ^ y[k][3]);
-        other = __builtin_amdgcn_ballot_w64(d != 0) != 0;
       }
-      if (other && lane == 0)
-        __hip_atomic_store(&differs[i], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t d = 0;
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        d |= (x[k][0] ^ y[k][0]) | (x[k][1] ^ y[k][1]) | (x[k][2] ^ y[k][2]) | (x[k][3] ^ y[k][3]);
+      other = __builtin_amdgcn_ballot_w64(d != 0) != 0;
     }
+    if (other && lane == 0)
+      __hip_atomic_store(&differs[i], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -684,7 +685,7 @@ hipError_t launch_mask_hash_prep(const SetDesc& s, const HashLayout& lay, const 
                      s.H, s.d, keys, mask,
                      reinterpret_cast<int64_t*>(ws + lay.off_tables),
                      reinterpret_cast<int32_t*>(ws + lay.off_arrived), ct ? ct->lead : nullptr,
-                     ct ? ct->differs : nullptr);
+                     ct ? ct->differs : nullptr, ct ? ct->end : nullptr);
   return hipGetLastError();
 }
 
@@ -694,7 +695,7 @@ hipError_t launch_copies(const SetDesc& s, const HashLayout& lay, const CopyTabl
   const int64_t full = (lay.tasks + (kBlock / 64) - 1) / (kBlock / 64);
   const int64_t cap = (int64_t)device_cu_count() * 4;
   hipLaunchKernelGGL(copy_kernel, dim3((uint32_t)(full < cap ? full : cap)), dim3(kBlock), 0,
-                     stream, s.table_dev, s.n, s.stride, token_bytes_of(s), s.L, ct.lead,
+                     stream, s.table_dev, s.n, s.stride, token_bytes_of(s), ct.lead, ct.end,
                      ct.differs);
   return hipGetLastError();
 }

@@ -132,13 +132,31 @@ RenderLayout render_layout(const SetDesc& s);
 int64_t render_units(const SetDesc& s, int64_t T_out);
 
 // Re-deliveries known by their bytes (key_mask.h): tables of n entries in the
-// workspace, in the room of the unit render's source bases, which the fused path
-// does not use.
+// workspace, in the room of the unit render's source bases (at least 16 bytes a
+// delivery), which the fused path does not use.
 struct CopyTables {
   const double* keys;
-  int32_t* lead;
-  int32_t* differs;
+  int32_t* lead;          // first delivery of the same key and length
+  int32_t* differs;       // 1: not that one's bytes
+  int32_t* end;           // stripes to compare of deliveries 0 .. i (inclusive prefix sums)
 };
+inline CopyTables copy_tables(const double* keys, void* room, int32_t n) {
+  int32_t* t = static_cast<int32_t*>(room);
+  return CopyTables{keys, t, t + n, t + 2 * n};
+}
+
+// Stripe `task` of those that a set's deliveries are compared by: the delivery whose
+// range of end[] holds it, and the stripe's number within it (tensor, stripe).
+__host__ __device__ __forceinline__ int copy_task(const int32_t* __restrict__ end, int32_t n,
+                                                  int64_t task, int64_t* local) {
+  int lo = 0, hi = n - 1;                  // the first i with end[i] > task
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (end[mid] > task) hi = mid; else lo = mid + 1;
+  }
+  *local = task - (lo > 0 ? end[lo - 1] : 0);
+  return lo;
+}
 
 // Launchers (enqueue on `stream`, return the first HIP error).
 // select == nullptr hashes every fragment; otherwise only fragments i with

@@ -37,10 +37,14 @@ struct Copies {
 __device__ __forceinline__ void equal_key_mask_body(int32_t n, const double* __restrict__ keys,
                                                     uint8_t* __restrict__ mask,
                                                     const int64_t* __restrict__ table = nullptr,
-                                                    int64_t stride = 0, int32_t* lead = nullptr,
-                                                    int32_t* differs = nullptr) {
+                                                    int64_t stride = 0, int64_t token_bytes = 0,
+                                                    int32_t L = 0, int32_t* lead = nullptr,
+                                                    int32_t* differs = nullptr,
+                                                    int32_t* end = nullptr) {
   __shared__ double s_key[1024];
+  __shared__ int32_t s_end[1024];
   const int tid = threadIdx.x;
+  int32_t stripes = 0;                     // to compare of this delivery
   double key = 0.0;
   if (tid < n) {
     key = keys[tid];
@@ -61,8 +65,21 @@ __device__ __forceinline__ void equal_key_mask_body(int32_t n, const double* __r
         }
       lead[tid] = l;
       differs[tid] = 0;
+      if (l != tid) stripes = (int32_t)(2 * L * stripes_of(len * token_bytes));
     }
   }
+  if (!lead) return;
+  // their running total, unless there is nothing to compare
+  const bool any = __syncthreads_or(stripes != 0);
+  s_end[tid] = stripes;
+  __syncthreads();
+  for (int o = 1; any && o < (int)blockDim.x; o <<= 1) {
+    const int32_t t = tid >= o ? s_end[tid - o] : 0;
+    __syncthreads();
+    s_end[tid] += t;
+    __syncthreads();
+  }
+  if (tid < n) end[tid] = s_end[tid];
 }
 
 }  // namespace cm

@@ -18,6 +18,7 @@
 
 #include "blake3.h"
 #include "fused_geometry.h"
+#include "internal.h"
 #include "paged_plan.h"
 #include "render_geometry.h"
 
@@ -274,6 +275,27 @@ int64_t hc_paged_fused_check(int32_t n_u, const int64_t* T, const int64_t* off,
   for (uint8_t z : seen)
     if (!z) ++bad;
   return bad;
+}
+
+// The stripes that a set's deliveries are compared by (copy_task), taken by `waves`
+// waves in turn: counts[i][k] times stripe k of delivery i (rows of `most` entries).
+// Returns the largest number of stripes that one wave takes, or -1 for a stripe
+// outside its delivery.
+int64_t hc_copy_tasks(const int32_t* end, int32_t n, int64_t waves, int32_t most,
+                      int32_t* counts) {
+  int64_t longest = 0;
+  for (int64_t w = 0; w < waves; ++w) {
+    int64_t mine = 0;
+    for (int64_t task = w; task < end[n - 1]; task += waves, ++mine) {
+      int64_t local = -1;
+      const int i = cm::copy_task(end, n, task, &local);
+      const int32_t have = end[i] - (i > 0 ? end[i - 1] : 0);
+      if (i < 0 || i >= n || local < 0 || local >= have || local >= most) return -1;
+      ++counts[(int64_t)i * most + local];
+    }
+    longest = mine > longest ? mine : longest;
+  }
+  return longest;
 }
 
 // The guard of the paged table kernel (paged_plan_usable) by a workgroup of nt

@@ -125,3 +125,44 @@ def test_deliveries_are_compared_from_256_mib_on(n, T, compares):
         cm.timing_reset()
     assert launches == 1 + compares
     assert res.n_unique == n - 3
+
+
+@pytest.mark.parametrize("n,copies,T", [(300, 120, 257), (1024, 1000, 256), (65, 40, 2100)])
+def test_many_deliveries_against_the_serial_pipeline(n, copies, T):
+    """More deliveries than a wave has lanes: copies, damaged copies (the first, a
+    middle and the last bytes), a pair with equal K and copies of one of it."""
+    dl = _many(n, copies, T, seed=n)
+    rng = np.random.default_rng(n)
+    for k, i in enumerate(rng.choice(n, size=9, replace=False)):
+        dl[i] = _clone(dl[i])
+        x = dl[i][(0, 1, -1)[k % 3]][1].view(torch.int32).view(-1)
+        x[(0, x.numel() // 2, -1)[k % 3]] ^= 1 << k
+    a, b, c = (int(i) for i in rng.choice(n, size=3, replace=False))
+    dl[b] = tuple((k.clone(), v.flip(2).contiguous()) for k, v in dl[a])
+    dl[c] = _clone(dl[b])
+    batch = cm.FragmentBatch(dl)
+    assert sum(batch.fragment_bytes(i) for i in range(n)) >= 256 << 20
+    want = cm.render_deliveries(batch, 1, 1e6, pipeline="serial")
+    got = cm.render_deliveries(batch, 1, 1e6)
+    assert got.digests == want.digests
+    assert np.array_equal(got.plan, want.plan)
+    assert torch.equal(got.merged.view(torch.int16), want.merged.view(torch.int16))
+
+
+def test_many_small_copies_take_no_longer_than_hashing_them():
+    """1000 copies of 1 MiB, 16 stripes each: compared by the whole chip (they took
+    fifteen times as long with each delivery's stripes on the same few waves)."""
+    batch = cm.FragmentBatch(_many(1024, 1000, 256, seed=2))
+    time = {}
+    for pipeline in ("fused", "serial") * 2:
+        cm.render_deliveries(batch, 1, 1e6, pipeline=pipeline).plan
+        t = []
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            cm.render_deliveries(batch, 1, 1e6, pipeline=pipeline).plan
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        time[pipeline] = min(t)
+    assert time["fused"] < 2 * time["serial"], time

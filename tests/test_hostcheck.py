@@ -120,3 +120,20 @@ def test_paged_plan_guard_by_every_thread(hc, status, n_unique, T_out, want, fre
     assert fresh_out[0] == fresh
     assert tasks[0] == (0 if refused else 77) and hsel.tolist() == [int(refused)] * n
     assert plan[C.PLAN_STATUS] == (C.CM_ESHAPE if refused else status)
+
+
+@pytest.mark.parametrize("waves", [1, 7, 4096])
+@pytest.mark.parametrize("stripes", [[0], [5], [0, 0, 0], [0, 3, 0, 0, 1, 0], [16] * 1000 + [0],
+                                     [0] + [700] * 6, list(range(64)) + [0] * 3])
+def test_compared_stripes_are_shared_evenly(hc, stripes, waves):
+    """Every stripe of every compared delivery is taken once, and no wave takes more
+    than its share, however many deliveries there are and however small they are."""
+    end = np.cumsum(stripes).astype(np.int32)
+    most = max(max(stripes), 1)
+    counts = np.zeros((len(stripes), most), np.int32)
+    hc.hc_copy_tasks.restype = ctypes.c_int64
+    hc.hc_copy_tasks.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32,
+                                 ctypes.c_void_p]
+    longest = hc.hc_copy_tasks(end.ctypes.data, len(stripes), waves, most, counts.ctypes.data)
+    assert longest == -(-sum(stripes) // waves)
+    assert counts.tolist() == [[1] * k + [0] * (most - k) for k in stripes]
