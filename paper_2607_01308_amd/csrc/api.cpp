@@ -637,9 +637,9 @@ int32_t render_deliveries_common(const cm_fragset* set, int32_t routing_layer, i
   // (Bytes, not stripes: a deep model's short tensors are many stripes and little
   // to hash.)
   uint8_t* rws = ws + cm::align_up(hlay.bytes, cm::kWsAlign);
-  const cm::CopyTables tables = cm::copy_tables(keys_dev, rws + rlay.off_src_base, s.n);
+  const cm::Copies tables = cm::copy_tables(rws + rlay.off_src_base, s.n);
   const bool large = T_all * cm::token_bytes_of(s) * 2 * s.L >= kCopyBytes;
-  const cm::CopyTables* ct = s.n > 1 && large ? &tables : nullptr;
+  const cm::Copies* ct = s.n > 1 && large ? &tables : nullptr;
   // the last score levels, the key mask and the hash trees' node tables in one
   // launch (the tables depend only on the lengths); it reads the score partials
   // before it writes over them

@@ -113,14 +113,14 @@ __global__ __launch_bounds__(1024) void mask_hash_prep_kernel(
     const int64_t* __restrict__ table, int32_t n, int64_t stride, int64_t token_bytes, int32_t L,
     int32_t levels, const double* parts, int64_t count, KnormDirect kd, int32_t H, int32_t d,
     double* keys, uint8_t* __restrict__ mask, int64_t* base, int32_t* __restrict__ arrived,
-    int32_t* lead, int32_t* differs, int32_t* end) {
+    Copies copies) {
   knorm_finish(table, stride, n, H, d, kd, parts, count, keys);
-  equal_key_mask_body(n, keys, mask, table, stride, token_bytes, L, lead, differs, end);
+  equal_key_mask_body(n, keys, mask, table, stride, token_bytes, L, copies);
   hash_tables(table, n, stride, token_bytes, L, levels, base, arrived);
 }
 
-// differs[i] = 1 for every delivery i whose bytes are not those of lead[i] (the
-// same length). Bound by HBM: both are read once, where hashing them costs the
+// Marks every delivery whose bytes are not those of its lead (the same length) and
+// counts it among its key's distinct ones. Bound by HBM: both are read once, where hashing them costs the
 // VALU more than that and the copies would be hashed to no other use (1.16 GB of
 // deliveries with equal keys, six of ten of them copies: hashing them and their
 // trees took 340 us, and the whole path 721; with this it takes 628). A wave
@@ -129,18 +129,16 @@ __global__ __launch_bounds__(1024) void mask_hash_prep_kernel(
 // that many small ones fill the chip as one large one does.
 __global__ __launch_bounds__(kBlock) void copy_kernel(const int64_t* __restrict__ table, int32_t n,
                                                       int64_t stride, int64_t token_bytes,
-                                                      const int32_t* __restrict__ lead,
-                                                      const int32_t* __restrict__ end,
-                                                      int32_t* differs) {
+                                                      Copies copies) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wave
   const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
-  const int64_t total = end[n - 1];
+  const int64_t total = copies.end[n - 1];
   for (int64_t task = (int64_t)blockIdx.x * (kBlock / 64) + wave; task < total; task += waves) {
     int64_t local;
-    const int i = copy_task(end, n, task, &local);
-    if (__hip_atomic_load(&differs[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) continue;
-    const int l = lead[i];
+    const int i = copy_task(copies.end, n, task, &local);
+    const int l = __hip_atomic_load(&copies.lead[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (l < 0) continue;                 // known to differ
     const int64_t bytes = table[(int64_t)i * stride] * token_bytes;
     const int64_t stripes = stripes_of(bytes);
     const int64_t t = local / stripes;
@@ -166,12 +164,12 @@ __global__ __launch_bounds__(kBlock) void copy_kernel(const int64_t* __restrict_
         d |= (x[k][0] ^ y[k][0]) | (x[k][1] ^ y[k][1]) | (x[k][2] ^ y[k][2]) | (x[k][3] ^ y[k][3]);
       other = __builtin_amdgcn_ballot_w64(d != 0) != 0;
     }
-    if (other && lane == 0)
-      __hip_atomic_store(&differs[i], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (other && lane == 0 && atomicOr(&copies.lead[i], kCopyDiffers) >= 0)
+      atomicAdd(&copies.distinct[copies.head[i]], 1);
   }
 }
 
-// Whether the Id of delivery i (the same on every lane) is computed in this pass:
+// Whether the Id of delivery i is computed in this pass:
 // those with select[i] == want, of them before the order only the needed ones
 // (key_mask.h).
 struct HashPass {
@@ -179,9 +177,9 @@ struct HashPass {
   uint32_t want;
   bool early;        // the pass before the order, with copies known
   Copies copies;
-  __device__ __forceinline__ bool takes(int i, int32_t n, int lane) const {
+  __device__ __forceinline__ bool takes(int i) const {
     if (select && select[i] != want) return false;
-    return !early || copies.needed(i, n, lane);
+    return !early || copies.needed(i);
   }
 };
 
@@ -204,7 +202,7 @@ __global__ __launch_bounds__(kBlock) void hash_chunk_kernel(const int64_t* __res
   for (int64_t task = (int64_t)blockIdx.x * (kBlock / 64) + wave; task < total_tasks;
        task += waves) {
     const int i = find_fragment(task_base, n, task);
-    if (!pass.takes(i, n, lane)) continue;
+    if (!pass.takes(i)) continue;
     const int64_t bytes = table[(int64_t)i * stride] * token_bytes;
     const int64_t stripes = stripes_of(bytes);
     const int64_t m = chunks_of(bytes);
@@ -477,7 +475,7 @@ __device__ __forceinline__ void copy_digest(const Copies& copies, int i, int32_t
   for (int k = 0; k < 8; ++k)
     w[k] = __hip_atomic_load(&id[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   for (int j = i + 1 + lane; j < n; j += 64)
-    if (copies.lead[j] == i && copies.is_copy(j)) {
+    if (copies.lead[j] == i) {              // (marked ones are no copies)
       uint32_t* o = reinterpret_cast<uint32_t*>(digests + (int64_t)j * 32);
 #pragma unroll
       for (int k = 0; k < 8; ++k) o[k] = w[k];
@@ -517,7 +515,7 @@ __global__ __launch_bounds__(kSubLanes) void hash_tail_kernel(
   const int t = blockIdx.x;
   const int i = blockIdx.y;
   const int lane = threadIdx.x;
-  if (!pass.takes(i, n, lane)) return;       // uniform over the workgroup
+  if (!pass.takes(i)) return;       // uniform over the workgroup
   const int64_t m0 = chunks_of(table[(int64_t)i * stride] * token_bytes);
   const int64_t m = nodes_at(m0, v0);                  // <= 2^kTailLevels (checked by the host)
   int K = 0;                                           // r = 2^K nodes per lane
@@ -562,7 +560,7 @@ __global__ __launch_bounds__(64) void hash_final_kernel(
     const int64_t* __restrict__ base_last, int32_t n, HashPass pass,
     const uint8_t* __restrict__ roots, uint8_t* __restrict__ digests) {
   const int i = blockIdx.x;
-  if (!pass.takes(i, n, threadIdx.x)) return;   // uniform over the workgroup
+  if (!pass.takes(i)) return;   // uniform over the workgroup
   fragment_id((uint64_t)table[(int64_t)i * stride], sh, roots + base_last[i] * 32,
               digests + (int64_t)i * 32, threadIdx.x);
   copy_digest(pass.copies, i, n, digests, threadIdx.x);
@@ -618,9 +616,8 @@ hipError_t launch_hash_prep(const SetDesc& s, const HashLayout& lay, uint8_t* ws
 
 hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8_t* select,
                             uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
-                            const CopyTables* ct, bool early) {
-  HashPass pass{select, want, ct && early, {ct ? ct->keys : nullptr, ct ? ct->lead : nullptr,
-                                            ct ? ct->differs : nullptr}};
+                            const Copies* ct, bool early) {
+  const HashPass pass{select, want, ct && early, ct ? *ct : Copies{}};
   int64_t* base = reinterpret_cast<int64_t*>(ws + lay.off_tables);
   // the stripes' values are in buf0; each launch reads one buffer and writes the other
   uint8_t* buf[2] = {ws + lay.off_buf0, ws + lay.off_buf1};
@@ -672,7 +669,7 @@ hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8
 
 hipError_t launch_mask_hash_prep(const SetDesc& s, const HashLayout& lay, const KnormPartials& kp,
                                  double* keys, uint8_t* mask, uint8_t* ws, hipStream_t stream,
-                                 const CopyTables* ct) {
+                                 const Copies* ct) {
   ScopedTiming tm(K_KEY_MASK, stream);
   // at least n threads (the scans over fragments). Up to 64 fragments the node
   // tables take no scan with barriers, and four waves read the score partials in a
@@ -684,30 +681,26 @@ hipError_t launch_mask_hash_prep(const SetDesc& s, const HashLayout& lay, const 
                      s.stride, token_bytes_of(s), s.L, lay.levels, kp.parts, kp.count, kp.direct,
                      s.H, s.d, keys, mask,
                      reinterpret_cast<int64_t*>(ws + lay.off_tables),
-                     reinterpret_cast<int32_t*>(ws + lay.off_arrived), ct ? ct->lead : nullptr,
-                     ct ? ct->differs : nullptr, ct ? ct->end : nullptr);
+                     reinterpret_cast<int32_t*>(ws + lay.off_arrived), ct ? *ct : Copies{});
   return hipGetLastError();
 }
 
-hipError_t launch_copies(const SetDesc& s, const HashLayout& lay, const CopyTables& ct,
+hipError_t launch_copies(const SetDesc& s, const HashLayout& lay, const Copies& ct,
                          hipStream_t stream) {
   ScopedTiming tm(K_KEY_MASK, stream);
   const int64_t full = (lay.tasks + (kBlock / 64) - 1) / (kBlock / 64);
   const int64_t cap = (int64_t)device_cu_count() * 4;
   hipLaunchKernelGGL(copy_kernel, dim3((uint32_t)(full < cap ? full : cap)), dim3(kBlock), 0,
-                     stream, s.table_dev, s.n, s.stride, token_bytes_of(s), ct.lead, ct.end,
-                     ct.differs);
+                     stream, s.table_dev, s.n, s.stride, token_bytes_of(s), ct);
   return hipGetLastError();
 }
 
 hipError_t launch_hash(const SetDesc& s, const HashLayout& lay, const uint8_t* select,
                        uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
-                       bool tables_ready, const CopyTables* ct) {
+                       bool tables_ready, const Copies* ct) {
   hipError_t e = hipSuccess;
   if (!tables_ready && (e = launch_hash_prep(s, lay, ws, stream)) != hipSuccess) return e;
-  const HashPass pass{select, want, ct != nullptr, {ct ? ct->keys : nullptr,
-                                                    ct ? ct->lead : nullptr,
-                                                    ct ? ct->differs : nullptr}};
+  const HashPass pass{select, want, ct != nullptr, ct ? *ct : Copies{}};
   {
     int64_t* base = reinterpret_cast<int64_t*>(ws + lay.off_tables);
     const int64_t nb1 = s.n + 1;

@@ -133,16 +133,22 @@ int64_t render_units(const SetDesc& s, int64_t T_out);
 
 // Re-deliveries known by their bytes (key_mask.h): tables of n entries in the
 // workspace, in the room of the unit render's source bases (at least 16 bytes a
-// delivery), which the fused path does not use.
-struct CopyTables {
-  const double* keys;
-  int32_t* lead;          // first delivery of the same key and length
-  int32_t* differs;       // 1: not that one's bytes
+// delivery), which the fused path does not use. lead == nullptr: none are known.
+constexpr int32_t kCopyDiffers = (int32_t)0x80000000;
+struct Copies {
+  int32_t* lead;          // first delivery of i's key and length, | kCopyDiffers if its bytes are not i's
+  int32_t* head;          // first delivery of i's key
+  int32_t* distinct;      // at a head: deliveries of its key that are no copies
   int32_t* end;           // stripes to compare of deliveries 0 .. i (inclusive prefix sums)
+  __device__ __forceinline__ bool is_copy(int i) const { return lead[i] >= 0 && lead[i] != i; }
+  // whether the order reads the digest of i: another delivery of its key is no copy either
+  __device__ __forceinline__ bool needed(int i) const {
+    return !is_copy(i) && distinct[head[i]] > 1;
+  }
 };
-inline CopyTables copy_tables(const double* keys, void* room, int32_t n) {
+inline Copies copy_tables(void* room, int32_t n) {
   int32_t* t = static_cast<int32_t*>(room);
-  return CopyTables{keys, t, t + n, t + 2 * n};
+  return Copies{t, t + n, t + 2 * n, t + 3 * n};
 }
 
 // Stripe `task` of those that a set's deliveries are compared by: the delivery whose
@@ -164,23 +170,23 @@ __host__ __device__ __forceinline__ int copy_task(const int32_t* __restrict__ en
 // tables_ready: the node-base tables are already in ws (launch_mask_hash_prep).
 hipError_t launch_hash(const SetDesc& s, const HashLayout& lay, const uint8_t* select,
                        uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
-                       bool tables_ready = false, const CopyTables* ct = nullptr);
+                       bool tables_ready = false, const Copies* ct = nullptr);
 // ct (the pass before the order, after launch_copies): only the Ids the order
 // reads, and their copies'.
-hipError_t launch_copies(const SetDesc& s, const HashLayout& lay, const CopyTables& ct,
+hipError_t launch_copies(const SetDesc& s, const HashLayout& lay, const Copies& ct,
                          hipStream_t stream);
 // launch_equal_key_mask and launch_hash_prep in one launch, after folding the
 // score partials into keys (kp.count > 1).
 hipError_t launch_mask_hash_prep(const SetDesc& s, const HashLayout& lay, const KnormPartials& kp,
                                  double* keys, uint8_t* mask, uint8_t* ws, hipStream_t stream,
-                                 const CopyTables* ct = nullptr);
+                                 const Copies* ct = nullptr);
 // The stages of launch_hash: node-base tables, then (after the leaves) the
 // parent levels and the final Id.
 hipError_t launch_hash_prep(const SetDesc& s, const HashLayout& lay, uint8_t* ws,
                             hipStream_t stream);
 hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8_t* select,
                             uint32_t want, uint8_t* digests, uint8_t* ws, hipStream_t stream,
-                            const CopyTables* ct = nullptr, bool early = false);
+                            const Copies* ct = nullptr, bool early = false);
 hipError_t launch_equal_key_mask(const SetDesc& s, const double* keys, uint8_t* mask,
                                  hipStream_t stream);
 hipError_t launch_knorm(const SetDesc& s, const KnormLayout& lay, int32_t layer, int64_t tail_len,
@@ -200,7 +206,7 @@ hipError_t launch_order_render_prep(const SetDesc& s, const double* keys, const 
                                     int64_t* plan, const RenderLayout& rlay, double base,
                                     int32_t style, int32_t stripe_blocks, const uint8_t* select,
                                     uint8_t* rws, hipStream_t stream,
-                                    const CopyTables* ct = nullptr);
+                                    const Copies* ct = nullptr);
 // Render of a set of distinct fragments, steps 2-5 after the score partials:
 // one workgroup folds the scores (kp.count > 1), orders, and builds the unit
 // render's tables for T_out rows; a plan whose T_out differs (the set held
@@ -226,7 +232,7 @@ hipError_t launch_render_hash(const SetDesc& s, const HashLayout& hlay, const Re
                               const int64_t* plan_dev, double base, int32_t style,
                               const uint8_t* select, uint8_t* digests, void* out, uint8_t* ws,
                               hipStream_t stream, bool tables_ready = false,
-                              bool prep_ready = false, const CopyTables* ct = nullptr);
+                              bool prep_ready = false, const Copies* ct = nullptr);
 // Rows [row0, T_out) of every row block are rendered into `out`, whose row
 // blocks are T_cap rows long (row0 = 0, T_cap = T_out: the whole merged cache).
 struct RenderRange {

@@ -57,6 +57,7 @@ __device__ __forceinline__ void order_body(const int64_t* __restrict__ table, in
   __shared__ int32_t s_first[1024];   // first delivery with the same digest
   __shared__ int32_t s_rank[1024];    // slot of each distinct delivery
   __shared__ int32_t s_src[1024];     // delivery of each slot
+  __shared__ uint8_t s_copy[1024];    // a copy known by its bytes: it has no digest yet
   __shared__ int64_t s_slot_len[1024];
   const int tid = threadIdx.x;
   const bool live = tid < n;
@@ -71,6 +72,7 @@ __device__ __forceinline__ void order_body(const int64_t* __restrict__ table, in
     len = table[(int64_t)tid * stride];
     s_key[tid] = key;
     s_len[tid] = len;
+    s_copy[tid] = copies.lead && copies.is_copy(tid) ? 1 : 0;
   }
   const int bad = __syncthreads_or(live && !isfinite(key));
   if (bad) {
@@ -92,21 +94,19 @@ __device__ __forceinline__ void order_body(const int64_t* __restrict__ table, in
     return;
   }
   if (live) {
-    bool shared = false;
-    for (int j = 0; j < n; ++j) shared |= (j != tid && s_key[j] == key);
+    bool shared = copies.lead && copies.needed(tid);
+    for (int j = 0; !copies.lead && j < n; ++j) shared |= (j != tid && s_key[j] == key);
     if (shared) load_digest_be(digests, tid, mine);
   }
-  // copies known by their bytes have no digest yet
-  auto known = [&](int j) { return copies.lead && copies.is_copy(j); };
 
   // Absorption: the first arrival of each content is kept (copies share key,
   // length and digest).
   int first = tid;
   if (live) {
-    const bool mine_known = known(tid);
-    if (mine_known) first = copies.lead[tid];
-    for (int j = 0; dedupe && !mine_known && j < tid; ++j) {
-      if (s_key[j] != key || s_len[j] != len || known(j)) continue;
+    const bool copy = s_copy[tid] != 0;
+    if (copy) first = copies.lead[tid];
+    for (int j = 0; dedupe && !copy && j < tid; ++j) {
+      if (s_key[j] != key || s_len[j] != len || s_copy[j]) continue;
       uint32_t other[8];
       load_digest_be(digests, j, other);
       if (cmp_digest(other, mine) == 0) { first = j; break; }
@@ -206,17 +206,11 @@ __global__ __launch_bounds__(1024) void order_render_prep_kernel(
   write_plan(l, n, plan);
   render_tables(l, n, d, ep, style, base, stripe_blocks, tensor_pairs, token_bytes, select, hsel,
                 unit_base, angles, table, stride, 0, nullptr, nullptr, blockIdx.x, gridDim.x);
+  // of the deliveries with an equal key, those with no other content among them were
+  // not hashed before the order: each has a slot, and the render computes its Id too
   if (copies.lead && blockIdx.x == 0 && l[CM_PLAN_STATUS] == CM_OK) {
-    // of the deliveries with an equal key, those with no other content among them
-    // were not hashed before the order: the render computes their Ids too
-    __syncthreads();
-    const int s = threadIdx.x;
-    if (s < (int)l[CM_PLAN_NUNIQUE]) {
-      const int i = (int)l[CM_PLAN_HEADER + s];
-      bool needed = false;
-      for (int j = 0; j < n; ++j) needed |= copies.ties(i, j);
-      if (!needed) hsel[i] = 0;
-    }
+    const int i = threadIdx.x;
+    if (i < n && !copies.is_copy(i) && !copies.needed(i)) hsel[i] = 0;
   }
 }
 
@@ -300,7 +294,7 @@ hipError_t launch_order(const SetDesc& s, const double* keys, const uint8_t* dig
 hipError_t launch_order_render_prep(const SetDesc& s, const double* keys, const uint8_t* digests,
                                     int64_t* plan, const RenderLayout& rlay, double base,
                                     int32_t style, int32_t stripe_blocks, const uint8_t* select,
-                                    uint8_t* rws, hipStream_t stream, const CopyTables* ct) {
+                                    uint8_t* rws, hipStream_t stream, const Copies* ct) {
   ScopedTiming tm(K_ORDER, stream);
   // a workgroup of at least n threads (one per delivery); an angle pair per thread
   const int threads = order_threads(s.n);
@@ -311,8 +305,7 @@ hipError_t launch_order_render_prep(const SetDesc& s, const double* keys, const 
                      select ? rws + rlay.off_hsel : nullptr,
                      reinterpret_cast<int64_t*>(rws + rlay.off_tiles),
                      reinterpret_cast<double*>(rws + rlay.off_angles),
-                     Copies{ct ? ct->keys : nullptr, ct ? ct->lead : nullptr,
-                            ct ? ct->differs : nullptr});
+                     ct ? *ct : Copies{});
   return hipGetLastError();
 }
 

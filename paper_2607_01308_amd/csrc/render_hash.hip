@@ -678,7 +678,7 @@ hipError_t launch_render_hash(const SetDesc& s, const HashLayout& hlay, const Re
                               const int64_t* plan_dev, double base, int32_t style,
                               const uint8_t* select, uint8_t* digests, void* out, uint8_t* ws,
                               hipStream_t stream, bool tables_ready, bool prep_ready,
-                              const CopyTables* ct) {
+                              const Copies* ct) {
   uint8_t* hws = ws;
   uint8_t* rws = ws + align_up(hlay.bytes, kWsAlign);
   hipError_t e = hipSuccess;

@@ -166,3 +166,25 @@ def test_many_small_copies_take_no_longer_than_hashing_them():
             t.append(a.elapsed_time(b))
         time[pipeline] = min(t)
     assert time["fused"] < 2 * time["serial"], time
+
+
+def test_order_is_no_slower_where_copies_are_looked_for():
+    """The order of 1024 distinct deliveries, with re-deliveries known by their bytes
+    (1 GiB) and without (128 MiB): no delivery is walked for another one's copies (that
+    took 1.8 times as long)."""
+    best = {}
+    for T in (32, 256):
+        batch = cm.FragmentBatch(_many(1024, 0, T, seed=3))
+        for _ in range(5):
+            cm.timing_reset()
+            cm.timing_enable(True)
+            try:
+                cm.render_deliveries(batch, 1, 1e6).plan
+                torch.cuda.synchronize()
+                ms, launches = cm.timing_query("order")
+            finally:
+                cm.timing_enable(False)
+                cm.timing_reset()
+            assert launches == 1
+            best[T] = min(best.get(T, 1e9), ms)
+    assert best[256] < 1.4 * best[32], best
