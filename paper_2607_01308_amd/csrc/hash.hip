@@ -364,14 +364,13 @@ __device__ __forceinline__ void fold_children(const uint8_t* c, int cur, int64_t
 __global__ __launch_bounds__(kSubLanes) void hash_subtree_kernel(
     const int64_t* __restrict__ table, int32_t n, int64_t stride, int64_t token_bytes, int32_t v0,
     int32_t K, const int64_t* __restrict__ base_lo, const int64_t* __restrict__ base_hi,
-    int64_t total_hi, const uint8_t* __restrict__ select, uint32_t want,
-    const uint8_t* __restrict__ in, uint8_t* __restrict__ out) {
+    int64_t total_hi, HashPass pass, const uint8_t* __restrict__ in, uint8_t* __restrict__ out) {
   __shared__ uint32_t lds[(1 << (kSubLevels - 1)) * 8][kSubLanes];
   const int lane = threadIdx.x;
   const int64_t g = (int64_t)blockIdx.x * kSubLanes + lane;
   if (g >= total_hi) return;
   const int i = find_fragment(base_hi, n, g);
-  if (select && select[i] != want) return;
+  if (!pass.takes(i)) return;
   const int64_t m0 = chunks_of(table[(int64_t)i * stride] * token_bytes);
   const int64_t m_lo = nodes_at(m0, v0);
   const int64_t m_hi = nodes_at(m0, v0 + K);
@@ -639,7 +638,7 @@ hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8
     const int64_t grid = (total + kSubLanes - 1) / kSubLanes;
     hipLaunchKernelGGL(hash_subtree_kernel, dim3((uint32_t)grid), dim3(kSubLanes), 0, stream,
                        s.table_dev, s.n, s.stride, token_bytes_of(s), v0, K, base + v0 * nb1,
-                       base + (v0 + K) * nb1, total, select, want, buf[launch & 1],
+                       base + (v0 + K) * nb1, total, pass, buf[launch & 1],
                        buf[(launch + 1) & 1]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }

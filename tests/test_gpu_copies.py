@@ -63,13 +63,17 @@ def test_copies_against_the_serial_pipeline(dtype, T, seed):
     graph.close()
 
 
-def test_only_copies():
-    """Every delivery of a key is the same fragment: no digest is read before the order."""
-    w = synth.custom("same", L=8, H=8, d=128, lengths=(3000, 2999), seed=5)
+@pytest.mark.parametrize("L,lengths", [(8, (3000, 2999)), (1, (20000, 17))])
+def test_only_copies(L, lengths):
+    """Every delivery of a key is the same fragment: no digest is read before the order.
+    Tensors of 6 MB, and of 41 MB beside 35 KB, whose trees take a launch more, which
+    passes over the deliveries that were not hashed."""
+    w = synth.custom("same", L=L, H=8, d=128, lengths=lengths, seed=5)
     a, b = synth.make_fragments(w, device="cuda")
-    batch = cm.FragmentBatch([b, a, _clone(a), _clone(b), _clone(a)])
-    want = cm.render_deliveries(batch, 3, 1e6, pipeline="serial")
-    got = cm.render_deliveries(batch, 3, 1e6)
+    batch = cm.FragmentBatch([b, a, _clone(a), _clone(b), _clone(a), _clone(a)])
+    assert sum(batch.fragment_bytes(i) for i in range(batch.n)) > 256 << 20
+    want = cm.render_deliveries(batch, L // 2, 1e6, pipeline="serial")
+    got = cm.render_deliveries(batch, L // 2, 1e6)
     assert got.digests == want.digests and np.array_equal(got.plan, want.plan)
     assert torch.equal(got.merged.view(torch.int16), want.merged.view(torch.int16))
 
