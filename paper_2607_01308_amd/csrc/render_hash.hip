@@ -250,6 +250,7 @@ struct PagedAddr {
     a.j = 0;
     const int64_t first = table[2 * i + 1];
     const int32_t* tab = (t & 1) ? v_table : k_table;
+    wave_lds_order();                    // the task before has looked its rows up
     const int64_t q0 = (sidx * 64 + lane) * RPC;   // the chunk's first row in the tensor
     const int64_t rows = (int64_t)H * T;
     ChunkRow c = fused_chunk_row(sidx, lane, RB_SHIFT, T);
@@ -261,6 +262,7 @@ struct PagedAddr {
       col[(RPC + r) * 64] = dr;
       fused_chunk_next(c, T);
     }
+    wave_lds_order();                    // lanes look up each other's columns
     return a;
   }
 };
@@ -488,13 +490,13 @@ __device__ __forceinline__ void render_hash_body(
         __builtin_amdgcn_s_setprio(0);
         if (hashing) {
           u32x4 m0[4], m1[4];
-          __builtin_amdgcn_wave_barrier();   // the wave's LDS writes come before its reads
+          wave_lds_order();                  // the other lanes' pieces are written
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             m0[q] = *reinterpret_cast<const u32x4*>(stage_chunk + 16 * q);
             m1[q] = *reinterpret_cast<const u32x4*>(stage_chunk + 64 + 16 * q);
           }
-          __builtin_amdgcn_wave_barrier();   // and before the next line's writes
+          wave_lds_order();                  // before the next line goes to the same LDS
           compress_block(st, m0, chunk, flags(2 * k, kB3ChunkBlocks - 1));
           compress_block(st, m1, chunk, flags(2 * k + 1, kB3ChunkBlocks - 1));
         }
