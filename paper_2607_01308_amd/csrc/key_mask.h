@@ -34,10 +34,14 @@ __device__ __forceinline__ void equal_key_mask_body(int32_t n, const double* __r
   if (live) {
     key = keys[tid];
     s_key[tid] = key;
-    if (copies.lead) s_len[tid] = table[(int64_t)tid * stride];
-    s_distinct[tid] = 0;
+    if (copies.lead) {
+      s_len[tid] = table[(int64_t)tid * stride];
+      s_distinct[tid] = 0;
+    }
   }
-  const bool renders = !__syncthreads_or(live && !isfinite(key));
+  bool renders = true;
+  if (copies.lead) renders = !__syncthreads_or(live && !isfinite(key));
+  else __syncthreads();
   bool shared = false;
   if (live) {
     for (int j = 0; j < n; ++j) shared |= (j != tid && s_key[j] == key);
