@@ -27,9 +27,10 @@ __device__ __forceinline__ void load_block64(const uint8_t* p, uint32_t (&m)[16]
 
 // Chunk `lane` of a stripe: `stripe` points at the stripe's first byte,
 // stripe_blocks (<= 1024) 64-byte blocks follow; chunk k is blocks [16k, 16k+16)
-// (the last may be shorter) and has BLAKE3 chunk index chunk0 + k. root: the
+// (the last may be shorter) and has BLAKE3 chunk index chunk0 + k. LEVELS: b3_chunk's. root: the
 // tensor is this one chunk. Returns false (s untouched) for a lane past the
 // last chunk.
+template <int LEVELS>
 __device__ __forceinline__ bool hash_lane_chunk(B3Cv& s, const uint8_t* stripe,
                                                 int64_t stripe_blocks, int lane, uint64_t chunk0,
                                                 bool root) {
@@ -38,8 +39,8 @@ __device__ __forceinline__ bool hash_lane_chunk(B3Cv& s, const uint8_t* stripe,
   const int64_t nb =
       stripe_blocks - first < kB3ChunkBlocks ? stripe_blocks - first : kB3ChunkBlocks;
   const uint8_t* p = stripe + first * 64;
-  b3_chunk<kChunkLevels>(s, nb, chunk0 + (uint64_t)lane, root,
-           [&](int64_t b, uint32_t (&w)[16]) { load_block64(p + b * 64, w); });
+  b3_chunk<LEVELS>(s, nb, chunk0 + (uint64_t)lane, root,
+                   [&](int64_t b, uint32_t (&w)[16]) { load_block64(p + b * 64, w); });
   return true;
 }
 

@@ -187,6 +187,7 @@ struct HashPass {
 // stripe, 1 KiB of consecutive bytes (the tensor's last chunk may be shorter,
 // lanes past it idle). The grid is bounded (a few workgroups per CU) and strides
 // over all tasks.
+template <int LEVELS>
 __global__ __launch_bounds__(kBlock) void hash_chunk_kernel(const int64_t* __restrict__ table,
                                                             int32_t n, int64_t stride,
                                                             int64_t token_bytes,
@@ -214,13 +215,13 @@ __global__ __launch_bounds__(kBlock) void hash_chunk_kernel(const int64_t* __res
     const uint8_t* p = reinterpret_cast<const uint8_t*>(table[(int64_t)i * stride + 1 + t]) +
                        ((sidx * kStripeBlocks) << 6);
     B3Cv s;
-    hash_lane_chunk(s, p, in_stripe < kStripeBlocks ? in_stripe : kStripeBlocks, lane, chunk0,
-                    m == 1);
+    hash_lane_chunk<LEVELS>(s, p, in_stripe < kStripeBlocks ? in_stripe : kStripeBlocks, lane,
+                            chunk0, m == 1);
     const int64_t left = m - (int64_t)chunk0;
     put_cv(fold_lds[wave], s, lane);
-    stripe_nodes<kChunkLevels>(fold_lds[wave], (int)(left < 64 ? left : 64), level, stripes == 1,
-                               lane, nodes + (base_v[i] + t * nodes_at(m, level) +
-                                              ((sidx * kStripeChunks) >> level)) * 32);
+    stripe_nodes<LEVELS>(fold_lds[wave], (int)(left < 64 ? left : 64), level, stripes == 1, lane,
+                         nodes + (base_v[i] + t * nodes_at(m, level) +
+                                  ((sidx * kStripeChunks) >> level)) * 32);
   }
 }
 
@@ -230,6 +231,7 @@ __global__ __launch_bounds__(kBlock) void hash_chunk_kernel(const int64_t* __res
 // in the order of its dense [1, H, T, d] layout: lane k of a stripe walks chunk
 // k's blocks row by row through the pages (a 64-byte block never straddles a
 // row, rows being 64-byte multiples).
+template <int LEVELS>
 __global__ __launch_bounds__(kBlock) void paged_hash_chunk_kernel(
     const uint8_t* __restrict__ pool, int64_t P, int32_t H, int32_t b_shift, int32_t rb_shift,
     const int64_t* __restrict__ table, const int32_t* __restrict__ blocks, int32_t n,
@@ -282,12 +284,12 @@ __global__ __launch_bounds__(kBlock) void paged_hash_chunk_kernel(
       }
     };
     B3Cv st;
-    if (has) b3_chunk<kChunkLevels>(st, nb, (uint64_t)c, m == 1, load);
+    if (has) b3_chunk<LEVELS>(st, nb, (uint64_t)c, m == 1, load);
     const int64_t left = m - sidx * kStripeChunks;
     put_cv(fold_lds[wave], st, lane);
-    stripe_nodes<kChunkLevels>(fold_lds[wave], (int)(left < 64 ? left : 64), level, stripes == 1,
-                               lane, nodes + (base_v[i] + t * nodes_at(m, level) +
-                                              ((sidx * kStripeChunks) >> level)) * 32);
+    stripe_nodes<LEVELS>(fold_lds[wave], (int)(left < 64 ? left : 64), level, stripes == 1, lane,
+                         nodes + (base_v[i] + t * nodes_at(m, level) +
+                                  ((sidx * kStripeChunks) >> level)) * 32);
   }
 }
 
@@ -707,7 +709,12 @@ hipError_t launch_hash(const SetDesc& s, const HashLayout& lay, const uint8_t* s
     const int64_t full = (lay.tasks + (kBlock / 64) - 1) / (kBlock / 64);
     const int64_t cap = (int64_t)device_cu_count() * kLeafBlocksPerCu;
     const int64_t grid = full < cap ? full : cap;
-    hipLaunchKernelGGL(hash_chunk_kernel, dim3((uint32_t)grid), dim3(kBlock), 0, stream,
+    // at most one workgroup, a wave per SIMD, on each CU: plain compressions, since a
+    // wave alone only pays for the paired runs' priorities (one fragment of 56 stripes,
+    // the whole Id: 61.5 us in runs, 57.5 plain; of 224, 56.8 and 51.7)
+    const auto kern = full <= device_cu_count() ? hash_chunk_kernel<-1>
+                                                : hash_chunk_kernel<kChunkLevels>;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(kBlock), 0, stream,
                        s.table_dev, s.n, s.stride, token_bytes_of(s), lay.stripe_level,
                        base + lay.stripe_level * nb1,
                        base + (int64_t)(lay.levels + 1) * nb1, lay.tasks, pass, ws + lay.off_buf0);
@@ -730,7 +737,9 @@ hipError_t launch_hash_paged(const PagedDesc& p, const HashLayout& lay, const ui
     const int64_t cap =
         (int64_t)device_cu_count() * (blocks_per_cu > 0 ? blocks_per_cu : kLeafBlocksPerCu);
     const int64_t grid = full < cap ? full : cap;
-    hipLaunchKernelGGL(paged_hash_chunk_kernel, dim3((uint32_t)grid), dim3(kBlock), 0, stream,
+    const auto kern = full <= device_cu_count() ? paged_hash_chunk_kernel<-1>   // (launch_hash)
+                                                : paged_hash_chunk_kernel<kChunkLevels>;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(kBlock), 0, stream,
                        static_cast<const uint8_t*>(p.pool), p.pages, s.H, p.b_shift,
                        (int32_t)__builtin_ctzll((unsigned long long)s.row_bytes), s.table_dev,
                        p.blocks_dev, s.n, token_bytes_of(s), lay.stripe_level,

@@ -50,3 +50,16 @@ def test_ids_of_tensors_beyond_the_top_launch():
     want = _ids(frags)
     assert cm.fragment_ids(frags) == want
     assert cm.render_deliveries(frags, 0, 1e6).digests == want
+
+
+# 2 x 512 stripes: a chunk grid of a wave per SIMD of 256 compute units, and one of more
+@pytest.mark.parametrize("T", [131072, 131073])
+def test_ids_around_one_wave_per_simd(T):
+    w = synth.custom("grid", L=1, H=1, d=128, lengths=(T,), seed=T)
+    frags = synth.make_fragments(w, device="cuda")
+    want = _ids(frags)
+    assert cm.fragment_ids(frags) == want
+    pool, lengths, lists, free = synth.make_paged(frags, 64, 2 * (T // 64 + 2))
+    r = cm.render_paged_set(cm.PagedSet(pool, lengths, lists), 0, 1e6, free, fused=False)
+    torch.cuda.synchronize()
+    assert [bytes(x) for x in r.digests_dev.cpu().numpy()] == want
