@@ -569,7 +569,7 @@ __global__ __launch_bounds__(64) void hash_final_kernel(
 
 }  // namespace
 
-constexpr int64_t kFoldAllStripes = 131072;
+constexpr int64_t kFoldAllStripes = 163840;   // 10 GiB
 
 HashLayout hash_layout(const SetDesc& s) {
   HashLayout lay{};
@@ -584,10 +584,12 @@ HashLayout hash_layout(const SetDesc& s) {
   while (((int64_t)1 << lay.levels) < max_m0) ++lay.levels;
   // How far a wave folds its stripe. Stripes that are whole tensors: to the root
   // (no launch between the chunks and the Id). Otherwise to two nodes: the sixth
-  // level would make one parent with the whole wave. From some 8 GiB of tensors on
-  // waves are never idle, and the upper levels, which use a part of the lanes, are
-  // left to a launch that uses all (level 3 against 5: Qwen3-4B large 16.12 against
-  // 16.29 ms, Qwen3-4B N=4 with 2.4 GB 1.124 against 1.109 ms).
+  // level would make one parent with the whole wave. On the largest sets waves are
+  // never idle, and the upper levels, which use a part of the lanes, are left to a
+  // launch that uses all. Whole path, level 3 / 5, medians of three runs of either:
+  // 2.4 GB 1044 / 1031 us, 7 GB 2859 / 2821, 9 GB 3840 / 3725, 12 GB 4787 / 4847,
+  // 18 GB 7254 / 7295, 27 GB 10121 / 10214, 39 GB 15.94 / 16.17 ms (runs of one side
+  // differ by 1 to 3%: the sign is sure at either end, the line lies where it turns).
   lay.stripe_level = lay.levels <= 6 ? lay.levels : lay.tasks > kFoldAllStripes ? 3 : 5;
   if (lay.levels == 0) lay.total1 = 0;
   size_t off = 0;
