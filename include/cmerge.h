@@ -290,8 +290,9 @@ int32_t cm_render_merge_hash(const cm_fragset* set, const int64_t* plan_dev,
 /* Steps 1-5 over a batch of deliveries (Render of Alg. 2 after Ingest of each
  * delivery), enqueued on `stream` in one call with nothing waiting for the host:
  * cm_fragment_knorm (keys_dev), cm_equal_key_mask (mask_dev), the Ids of the
- * deliveries whose keys collide (cm_fragment_hash_select with mask 1), the
- * dedupe and canonical order (plan_dev, as cm_canonical_order), then the render
+ * deliveries whose keys collide (cm_fragment_hash_select with mask 1; from 256 MiB
+ * of deliveries on, byte copies among them are found by comparison and share the
+ * Id of the first, and the render computes those that no tie needs), the dedupe and canonical order (plan_dev, as cm_canonical_order), then the render
  * fused with every other Id (cm_render_merge_hash), reading the plan on the
  * device. The merged cache of the plan's length T_out is written to the start of
  * out_dev as [L][2][1][H][T_out][d] (each layer's K then V), so out_dev must hold
@@ -491,7 +492,10 @@ int32_t cm_paged_workspace_size(const cm_pagedset* set, size_t* bytes_out);
  * to the per-kernel totals and returns the total milliseconds and launch count
  * for one kernel name ("hash_prep", "hash_leaf", "hash_parent", "hash_final",
  * "knorm_rows", "knorm_tree", "order", "key_mask", "render_prep", "render",
- * "render_hash", "paged", "paged_hash_render"). */
+ * "render_hash", "paged", "paged_hash_render"). "hash_parent" is the trees above the
+ * stripes that the chunk kernels fold, with the Ids where one launch makes both and
+ * where tensors of 2 to 64 chunks leave only the Ids to make; "hash_final" the Ids
+ * otherwise. "key_mask" includes the comparison of re-deliveries. */
 int32_t cm_timing_enable(int32_t on);
 int32_t cm_timing_reset(void);
 int32_t cm_timing_query(const char* kernel, double* total_ms, int64_t* launches);

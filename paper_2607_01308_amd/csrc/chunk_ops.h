@@ -7,7 +7,7 @@
 
 namespace cm {
 
-// The chunk kernels keep four waves on a SIMD (101 VGPRs): the levels that pair
+// The chunk kernels keep four waves on a SIMD (114 VGPRs): the levels that pair
 // best there (b3_step_paired). 2.4 GB of chunks, four waves: b3_compress 778 us,
 // levels 0 575 us, levels 1 570 us; 2.97 GB inside the Qwen3-4B large set's path
 // 1071 -> 783 us.

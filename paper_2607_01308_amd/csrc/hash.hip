@@ -30,9 +30,9 @@ namespace cm {
 namespace {
 
 constexpr int kBlock = 256;
-// Grid of CUs x CM_HASH_BLOCKS_PER_CU workgroups of 4 waves (3 fit on a SIMD at
-// this kernel's register count); measured on 2.7 GB of hashing: 2 per CU
-// 1.10 ms, 3 per CU 1.06 ms, 4 per CU 1.03 ms.
+// Grid of CUs x CM_HASH_BLOCKS_PER_CU workgroups of 4 waves, as many as fit (four
+// waves on a SIMD at this kernel's 114 VGPRs); measured on 2.7 GB of hashing, with
+// plain compressions: 2 per CU 1.10 ms, 3 per CU 1.06 ms, 4 per CU 1.03 ms.
 #ifndef CM_HASH_BLOCKS_PER_CU
 #define CM_HASH_BLOCKS_PER_CU 4
 #endif
@@ -554,8 +554,9 @@ __global__ __launch_bounds__(kSubLanes) void hash_tail_kernel(
   if (lane == 0) arrived[i] = 0;
 }
 
-// The Id alone (every tensor of the set is a single chunk, so there is no tail
-// launch to compute it), one workgroup per fragment.
+// The Id alone, one workgroup per fragment: where the chunk kernels' stripes are
+// whole tensors (up to 64 chunks each), so that no tail launch follows them, and
+// after the tail launch of sets of more than kFuseIdMaxGroups tensors.
 __global__ __launch_bounds__(64) void hash_final_kernel(
     const int64_t* __restrict__ table, int64_t stride, IdShape sh,
     const int64_t* __restrict__ base_last, int32_t n, HashPass pass,
@@ -628,8 +629,8 @@ hipError_t launch_hash_tree(const SetDesc& s, const HashLayout& lay, const uint8
   hipError_t e = hipSuccess;
   int launch = 0;
   int v0 = lay.stripe_level;
-  // where the chunk kernels' stripes are whole tensors, the Ids' launch is all
-  // that is left of the trees, and is timed as such
+  // where the chunk kernels' stripes are whole tensors (of more than a chunk), the
+  // Ids' launch is all that is left of the trees, and is timed as hash_parent
   const int id_timer = lay.levels > 0 && v0 == lay.levels ? K_HASH_PARENT : K_HASH_FINAL;
   // three levels per launch over all tensors while more than kTailLevels remain
   // (every tensor then has at most 2^kTailLevels nodes), then the rest at once

@@ -19,8 +19,8 @@
 // all rows lie in the same columns, so its angles are a few registers.
 //
 // What bounds it: HBM, in this access pattern. 36,864 stripes of 64 KiB copied
-// by waves that walk them in lines reach 5.4 TB/s read + written whatever the
-// line's width (128 B to 512 B: 5.35-5.6), one-wave units in address order 6.0-6.7,
+// by waves that walk them in lines, as many waves as here, reach 5.4-5.55 TB/s read +
+// written whatever the line's width (128 to 512 B), one-wave units in address order 6.1-6.7,
 // but a chunk's 16 dependent compressions keep its line open for tens of
 // microseconds, so the stripes in flight (three waves per SIMD: 192 MB) cannot be
 // fewer. On 4.83 GB (Qwen3-4B N=4) the kernel takes 950 us: 925 us with neither

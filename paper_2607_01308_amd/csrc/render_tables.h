@@ -1,6 +1,6 @@
-// Per-slot tables of the render, built by one workgroup once the plan exists
-// (shared by the render's own prep kernel and the order kernels of the one-call
-// paths, which build them right after the plan, in the same workgroup).
+// Per-slot tables of the render, built once the plan exists (shared by the render's
+// own prep kernel, one workgroup, and the order kernels of the one-call paths, whose
+// workgroups each hold the plan and take a share).
 #pragma once
 
 #include "render_geometry.h"
@@ -8,10 +8,11 @@
 
 namespace cm {
 
-// One workgroup: per-slot cos/sin(off_s * theta_j), theta_j = base^(-2j/d), in
+// Per-slot cos/sin(off_s * theta_j), theta_j = base^(-2j/d), in
 // fp64: in the piece-ordered layout of rotate.h for the unit render
 // (stripe_blocks == 0), in pair order (entry j holds pair j) for the fused
-// hash+render, whose lanes read them wave-uniformly. With stripe_blocks > 0 also the
+// hash+render, whose lanes each read their own pieces' pairs (a tensor's last stripe,
+// where all lanes are at the same block, reads them wave-uniformly). With stripe_blocks > 0 also the
 // per-slot work-unit bases of the fused hash+render (2L * stripes of that many
 // 64-byte blocks per slot, exclusive scan; the total at index n as well, none if
 // the plan's status is an error) and, with a select mask, hsel[i] = 0
