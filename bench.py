@@ -17,9 +17,11 @@ computed at ingest), the path whose bytes are all HBM streaming.
 
 Prints one JSON line. `roofline` is for the kernel with the largest share of
 the step, measured with per-kernel HIP events on the launch stream over the
-timed steps: the fused hash+render kernel against the VALU issue rate (its
-algorithmic operations: 672 per hashed 64-byte block, 4 per rotated K
-element). `roofline_render` gives the render kernel of `render_set` against
+timed steps: the fused hash+render kernel against HBM bandwidth (the fragments'
+bytes read once, the merged cache written once), with its algorithmic VALU
+operations beside it (672 per hashed 64-byte block, 4 per rotated K element;
+their rate is no bound: half of BLAKE3's instructions issue beside another
+wave's). `roofline_render` gives the render kernel of `render_set` against
 HBM bandwidth. `cpu_baseline` times the CPU oracle on a bounded sample of the
 same workload.
 """
@@ -38,10 +40,10 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0                 # MI355X HBM3E
-VALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12  # 256 CUs x 64 lanes x 2.4 GHz: one 32-bit or fp64 op
 B3_OPS_PER_BLOCK = 672                 # BLAKE3: 7 rounds x 8 G x 12 VALU ops (add3, add, xor, alignbit)
 ROT_OPS_PER_ELEM = 4                   # widen, fp64 product, fp64 FMA, narrow
 OTHER_WORKLOADS = ("qwen3-4b-n4", "qwen3-1.7b-n5", "qwen3-1.7b-n2", "tiny")
+COMPARE_BYTES = 256 << 20              # deliveries from which byte copies are found by comparison
 MALL_BYTES = 256 << 20                 # MI355X Infinity Cache: inputs smaller than 4x this are
 ROTATE_TARGET = 4 * MALL_BYTES         # replicated and the steps cycle through the copies
 
@@ -76,14 +78,19 @@ def _traffic(kernel: str, workload: str):
     return t.get("hbm_bytes_per_launch")
 
 
-def fused_work(w, r, mask):
+def fused_work(w, r, mask, compared):
     """Algorithmic work of one fused launch: VALU ops (hash of every slot whose
     Id it computes, rotation of every K element at a non-zero offset) and the
-    bytes it must move."""
+    bytes hashed. The Ids computed before it: of deliveries whose score collides
+    (mask), or, where copies are found by comparison, of slots with equal scores."""
+    keys = r.keys
+    slots = [keys[i] for i in r.order]
+    early = {i for i in r.order
+             if (slots.count(keys[i]) > 1 if compared else int(mask[i]) != 0)}
     tok = w.L * w.H * w.d                       # elements per token per tensor kind
     esize = 2 if w.dtype == "bfloat16" else 4
     hashed_blocks = sum(2 * tok * T * esize // 64 for i, T in zip(r.order, r.lengths)
-                        if int(mask[i]) == 0)
+                        if i not in early)
     rotated = sum(tok * T for off, T in zip(r.offsets, r.lengths) if off != 0)
     return B3_OPS_PER_BLOCK * hashed_blocks + ROT_OPS_PER_ELEM * rotated, hashed_blocks * 64, rotated
 
@@ -558,26 +565,30 @@ def main():
         ws = torch.empty(cm.workspace_size(batch), dtype=torch.uint8, device=dev)
         cm.fragment_knorm(batch, w.routing_layer, r.tail_len, keys, ws)
         cm.equal_key_mask(batch, keys, mask)
-        ops, hashed_bytes, rotated = fused_work(w, r, mask.cpu().numpy())
+        mask = mask.cpu().numpy()
+        ops, hashed_bytes, rotated = fused_work(w, r, mask, w.delivery_bytes >= COMPARE_BYTES)
+        ops_paged = fused_work(w, r, mask, True)[0]   # (the pool holds the distinct ones)
         del r, ws
         pk = per_kernel["render_hash"]
         avg = pk["total_ms"] / pk["launches"] / 1e3
-        ach = ops / avg / 1e12
+        ach = render_bytes / avg / 1e9
         rooflines["render_hash"] = {
-            "bound": "alu", "achieved": round(ach, 3), "peak": round(VALU_PEAK_TOPS, 3),
-            "unit": "Tops/s", "frac": round(ach / VALU_PEAK_TOPS, 4),
-            "traffic": _traffic("render_hash", w.name),
-            "ops_per_launch": ops, "hashed_bytes": hashed_bytes, "rotated_elements": rotated,
-            "avg_ms": round(avg * 1e3, 4), "hbm_GBps": round(render_bytes / avg / 1e9, 1)}
-        # the fused paged kernel does the same work (same plan, same deliveries
-        # hashed, same elements rotated) on the pool
+            "bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
+            "frac": round(ach / HBM_PEAK_GBPS, 4), "traffic": _traffic("render_hash", w.name),
+            "bytes_per_launch": render_bytes, "avg_ms": round(avg * 1e3, 4),
+            "ops_per_launch": ops, "valu_Tops": round(ops / avg / 1e12, 3),
+            "hashed_bytes": hashed_bytes, "rotated_elements": rotated}
+        # the fused paged kernel on the pool: the same reads, the pages that are
+        # not in place already written
         pms = paged.get("set_steps_1_to_5", {}).get("kernels_ms", {}).get("paged_hash_render")
         if pms:
-            achp = ops / (pms / 1e3) / 1e12
+            pb = render_bytes // 2 + paged_bytes // 2
+            achp = pb / (pms / 1e3) / 1e9
             paged["set_steps_1_to_5"]["roofline"] = {
-                "kernel": "paged_hash_render", "bound": "alu", "achieved": round(achp, 3),
-                "peak": round(VALU_PEAK_TOPS, 3), "unit": "Tops/s",
-                "frac": round(achp / VALU_PEAK_TOPS, 4), "ops_per_launch": ops, "avg_ms": pms}
+                "kernel": "paged_hash_render", "bound": "hbm", "achieved": round(achp, 1),
+                "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achp / HBM_PEAK_GBPS, 4),
+                "bytes_per_launch": pb, "ops_per_launch": ops_paged,
+                "valu_Tops": round(ops_paged / (pms / 1e3) / 1e12, 3), "avg_ms": pms}
     if "render" in set_kernels:
         pk = set_kernels["render"]
         avg = pk["total_ms"] / pk["launches"] / 1e3

@@ -292,7 +292,8 @@ int32_t cm_render_merge_hash(const cm_fragset* set, const int64_t* plan_dev,
  * cm_fragment_knorm (keys_dev), cm_equal_key_mask (mask_dev), the Ids of the
  * deliveries whose keys collide (cm_fragment_hash_select with mask 1; from 256 MiB
  * of deliveries on, byte copies among them are found by comparison and share the
- * Id of the first, and the render computes those that no tie needs), the dedupe and canonical order (plan_dev, as cm_canonical_order), then the render
+ * Id of the first, and the render computes those that no tie needs), the
+ * dedupe and canonical order (plan_dev, as cm_canonical_order), then the render
  * fused with every other Id (cm_render_merge_hash), reading the plan on the
  * device. The merged cache of the plan's length T_out is written to the start of
  * out_dev as [L][2][1][H][T_out][d] (each layer's K then V), so out_dev must hold

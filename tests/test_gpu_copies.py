@@ -78,28 +78,35 @@ def test_only_copies(L, lengths):
     assert torch.equal(got.merged.view(torch.int16), want.merged.view(torch.int16))
 
 
-def test_colliding_ids_are_written_beside_a_non_finite_score():
-    dl = _groups("bfloat16", 1201)
-    bad = _clone(dl[-1])
-    bad[3][0][0, 0, -1, 0] = float("nan")
+@pytest.mark.parametrize("n", [12, 100])
+def test_colliding_ids_are_written_beside_a_non_finite_score(n):
+    if n == 12:
+        dl = _groups("bfloat16", 1201)
+        dl.append(_clone(dl[-1]))                # the only copies among those that collide
+    else:
+        dl = _many(n, 70, 800, seed=8)[1:]
+    layer = len(dl[0]) // 2
+    bad = tuple((k + 0, v + 0) for k, v in dl[1])
+    bad[layer][0][0, 0, -1, 0] = float("nan")
     dl.insert(4, bad)
-    dl.append(_clone(dl[-1]))                    # the only copies among those that collide
     batch = cm.FragmentBatch(dl)
-    assert sum(batch.fragment_bytes(i) for i in range(batch.n)) > 256 << 20
-    n, T = batch.n, sum(batch.lengths)
+    assert batch.n == n and sum(batch.fragment_bytes(i) for i in range(n)) > 256 << 20
+    T = sum(batch.lengths)
     keys = torch.empty(n, dtype=torch.float64, device="cuda")
     mask = torch.empty(n, dtype=torch.uint8, device="cuda")
     digests = torch.full((n, 32), 0xCD, dtype=torch.uint8, device="cuda")
     plan = torch.empty(cm.plan_elems(n), dtype=torch.int64, device="cuda")
     out = torch.full((batch.L * 2 * batch.H * T * batch.d,), 7.0, dtype=torch.bfloat16, device="cuda")
     ws = torch.empty(cm.workspace_size(batch), dtype=torch.uint8, device="cuda")
-    cm.render_deliveries_async(batch, 3, min(batch.lengths), 1e6, "half", keys, mask, digests, plan,
-                               out, T, ws)
+    cm.render_deliveries_async(batch, layer, min(batch.lengths), 1e6, "half", keys, mask, digests,
+                               plan, out, T, ws)
     assert int(plan[C.PLAN_STATUS]) == C.CM_ENONFINITE
     ids = cm.fragment_ids(dl)
     got = [bytes(r) for r in digests.cpu().numpy()]
     collide = mask.cpu().tolist()
-    assert collide == [1, 1, 1, 1, 0, 1, 1, 1, 1, 1, 1, 1]
+    scores = keys.cpu().tolist()
+    assert collide == [int(scores.count(k) > 1) for k in scores] and collide[4] == 0
+    assert sum(collide) >= n // 2
     assert got == [f if c else b"\xcd" * 32 for f, c in zip(ids, collide)]
     assert bool((out == 7.0).all())
 
